@@ -1374,9 +1374,18 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 }
 
 // 16 bytes per lane from buffer offset voff + soff (device-coherent) into LDS
-// at lds + 16 lane.
+// at lds + 16 lane.  The wait states are part of the asm: the compiler's
+// hazard pass does not look into it, and the hardware needs five between a
+// vector instruction that writes a scalar register (v_readlane, which restores
+// spilled descriptors, or v_readfirstlane) and a memory instruction that reads
+// it, and one between a write of M0 and an LDS DMA.  Without them a reload of
+// the descriptor right in front of the DMA sends it to a stale address: of the
+// exchange's instances only the one at H = 192 had such a reload, and it
+// faulted the device.
 __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
-  asm volatile("buffer_load_dwordx4 %0, %1, %2 offen sc1 lds" : : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
+  asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2 offen sc1 lds"
+               :
+               : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
                : "memory");
 }
 
