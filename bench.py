@@ -66,7 +66,8 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ("paper_2609_37899_amd/csrc/soma_kernels.hpp", "paper_2609_37899_amd/csrc/soma_rng.hpp")
+KERNEL_SOURCES = ("paper_2609_37899_amd/csrc/soma_kernels.hpp", "paper_2609_37899_amd/csrc/soma_xchg.hpp",
+                  "paper_2609_37899_amd/csrc/soma_rng.hpp")
 BODY_SOURCES = KERNEL_SOURCES + ("paper_2609_37899_amd/csrc/soma_body.hpp",)
 WIDE_SOURCES = BODY_SOURCES + ("paper_2609_37899_amd/csrc/soma_wide.hpp",)
 

@@ -117,10 +117,10 @@ enum soma_flags {
    * within the split products' rounding. */
   SOMA_FLAG_TILED_WEIGHTS = 2,
   /* Run the persistent recurrence with fp32 h staged by every block of a
-   * group, even where the pipelined split exchange applies (four row tiles
-   * in flight, h published once in split form and copied into LDS by DMA).
-   * Both form the same split products; the exchange adds the gate inputs
-   * after them rather than before, so results agree within that rounding. */
+   * group, even where the pipelined split exchange applies (B > 32: four row
+   * tiles in flight, h published once in split form and copied into LDS by
+   * DMA).  Both form the same split products; the exchange sums them in
+   * another order, so results agree within that rounding. */
   SOMA_FLAG_STAGED_RECURRENCE = 4,
   /* Store each layer's output sequence in fp32 and let the next layer's
    * streaming projection split it while staging it, even where the
@@ -246,8 +246,8 @@ void soma_destroy(soma_ctx* ctx);
  * expert; the seeds are a device array, so a step enqueues no host-to-device
  * copy and can be replayed without host work; and the step counter that keys
  * the probe stream is explicit.
- * Where the shape allows (H <= 704 and a multiple of 64, B <= 64, a device
- * that supports cooperative launches), each layer's recurrence runs as one persistent
+ * Where the shape allows (H <= 704 and a multiple of 64, a device that
+ * supports cooperative launches), each layer's recurrence runs as one persistent
  * launch whose blocks synchronise per time step through bounded waits; if a
  * wait ever times out, the step's losses are NaN and theta is left
  * unchanged.
@@ -269,9 +269,10 @@ int soma_spsa_step(soma_ctx* ctx, float* theta_dev, const uint64_t* seeds_dev, u
 /* soma_spsa_step for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * no context and no workspace.  The step's scratch space is a static device
- * array of the library, 32 MiB on each GPU it runs on, held until the
- * process ends; shapes whose workspace for one direction at a time exceeds
- * it return SOMA_ESHAPE (the tiny and small shapes fit: the N = 1, H = 64
+ * array of the library, 32 MiB on each GPU it runs on (and 24 MiB more for the
+ * exchange recurrence, which shapes are not held to), held until the process
+ * ends; shapes whose workspace for one direction at a time exceeds the 32 MiB
+ * return SOMA_ESHAPE (the tiny and small shapes fit: the N = 1, H = 64
  * workload needs 1.3 MB).  The directions run in the largest chunk that fits
  * (or cfg->pair_chunk).  Stacked LSTM only (SOMA_EINVAL for SOMA_ARCH_BODY).
  * Calls share that array on each GPU: calls that overlap on one GPU (two

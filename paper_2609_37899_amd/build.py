@@ -12,14 +12,12 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SRC = os.path.join(PKG, "csrc", "soma_api.hip")
-DEPS = [os.path.join(PKG, "csrc", f) for f in ("soma_api.hip", "soma_kernels.hpp", "soma_body.hpp", "soma_rng.hpp")] + \
-       [os.path.join(ROOT, "include", "soma.h")]
+SRCS = [os.path.join(PKG, "csrc", f) for f in ("soma_api.hip", "soma_rec.hip")]
 LIB = os.path.join(PKG, "libsoma.so")
 ARCH = os.environ.get("SOMA_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++20", "-fPIC",
     # The probe generator is specified operation by operation: no contraction.
     "-ffp-contract=off",
     # Packed fp32 VALU instructions (v_pk_*_f32) stay off: plain fp32 code
@@ -39,12 +37,24 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False) -> str:
+    """Compile the translation units side by side, then link them."""
     tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-           "-o", tmp, SRC]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd, cwd="/tmp")
+    objs = [tmp + ".%d.o" % i for i in range(len(SRCS))]
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc")]
+    cmds = [[hipcc(), *HIPCC_FLAGS, *inc, "-c", "-o", o, s] for s, o in zip(SRCS, objs)]
+    try:
+        for cmd in cmds if verbose else []:
+            print(" ".join(cmd), flush=True)
+        procs = [subprocess.Popen(cmd, cwd="/tmp") for cmd in cmds]
+        codes = [p.wait() for p in procs]
+        for code, cmd in zip(codes, cmds):
+            if code:
+                raise subprocess.CalledProcessError(code, cmd)
+        subprocess.check_call([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs], cwd="/tmp")
+    finally:
+        for o in objs:
+            if os.path.exists(o):
+                os.unlink(o)
     os.replace(tmp, LIB)
     return LIB
 

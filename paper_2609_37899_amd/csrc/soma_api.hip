@@ -9,7 +9,7 @@
 //                   k_rec_xchg stored its h pre-split (B % 16 = 0,
 //                   H = 128, 256, 512), else k_proj_stream; then the
 //                   recurrence:
-//                   k_rec_xchg (one cooperative launch, four row tiles of
+//                   k_rec_xchg (B > 32: one cooperative launch, row tiles of
 //                   the batch pipelined, h exchanged pre-split by LDS DMA)
 //                   or k_rec_persist (one cooperative launch; blocks of a
 //                   group share the recurrent weights and stage h each step),
@@ -26,7 +26,7 @@
 // forward in k_body (soma_body.hpp); the wide controls' body
 // (SOMA_ARCH_WIDE) forms each slot's perturbed weights once (k_wide_form)
 // and runs split-fp16 products (k_wide_mm), LayerNorms and the decoder
-// (soma_wide.hpp) around k_rec_persist on the pre-formed weights.  Every kernel that forms split fp16
+// (soma_wide.hpp) around k_rec_xchg or k_rec_persist on the pre-formed weights.  Every kernel that forms split fp16
 // weights checks their range and the persistent recurrence bounds its waits:
 // either failure sets a sticky flag, and the step is then aborted on the
 // device (NaN losses, theta untouched).  The step writes theta only in the
@@ -47,6 +47,7 @@
 #include "soma_kernels.hpp"
 #include "soma_body.hpp"
 #include "soma_wide.hpp"
+#include "soma_rec.hpp"
 
 namespace {
 
@@ -193,6 +194,9 @@ Layout layout_for_body(const soma_config& c, int pc) {
   return L;
 }
 
+void add_xchg(const soma_config& c, Layout* L, size_t* at);
+int64_t gin_rows(const soma_config& c);
+
 // The wide controls' body: per slot of a pass its pre-formed weights, the
 // per-byte input projection U, the residual stream x, the normalised rows
 // (shared with the recurrence's h: each reader is done before the next
@@ -217,10 +221,11 @@ Layout layout_for_wide(const soma_config& c, int pc) {
   L.U = at; at += round_up(sizeof(float) * slots * SOMA_VOCAB * dp);
   L.xres = at; at += round_up(sizeof(float) * slots * R * dp);
   L.hseq = at; at += round_up(sizeof(float) * slots * R * dp);
-  L.gin = at; at += round_up(sizeof(float) * slots * R * 4 * dp);
+  L.gin = at; at += round_up(sizeof(float) * slots * gin_rows(c) * 4 * dp);
   L.fdec = at; at += round_up(sizeof(float) * N * R * E);
   L.lse = at; at += round_up(sizeof(float) * N * R);
   L.dpart = at; at += round_up(sizeof(float) * N * L.delta_chunks * SOMA_VOCAB * E);
+  add_xchg(c, &L, &at);
   L.total = at;
   return L;
 }
@@ -228,32 +233,55 @@ Layout layout_for_wide(const soma_config& c, int pc) {
 bool stream_weights(const soma_config& c);
 bool local_embedding(const soma_config& c);
 
-// The pipelined exchange recurrence (k_rec_xchg) runs for the stacked LSTM
-// with four row tiles (48 < B <= 64) at the widths it has been validated on:
-// H = 128, 256, 512 and 704.  At H = 192 a launch faulted the device, with no
-// cause found in the kernel's indexing; that width and the others not yet
-// validated take the staged recurrence.  Whether it runs also depends on the
-// device (compute units per XCD).
+// Width of the recurrence: the wide body runs it at its padded width.
+int rec_width(const soma_config& c) { return c.arch == SOMA_ARCH_WIDE ? soma::wide_padded(c.hidden) : c.hidden; }
+
+// Rows of one slot's gate inputs in the exchange recurrence's order: whole
+// tiles of 16 sequences for every time step.
+int64_t tile_rows(const soma_config& c) { return int64_t(c.seq_len - 1) * ((c.batch + 15) / 16) * 16; }
+
+// The pipelined exchange recurrence (k_rec_xchg) runs for batches beyond 32
+// sequences -- its pipeline needs four row tiles in flight, and with three of
+// them filled it is still ahead of the staged recurrence, which computes four
+// as well (H = 128, B = 33, 128 jobs of 99 steps: 0.81 against 0.98 ms a
+// layer) -- at every width its registers hold: H a multiple of 64 up to 704 (up to 512 on the wide body's pre-formed weights;
+// the stacked LSTM at H = 64 has k_rec_local).  Batches beyond 64 are cut into
+// jobs of 64.  It addresses a slot's gate inputs with 32-bit offsets.  Whether
+// it runs also depends on the device (compute units per XCD).
 bool xchg_shape(const soma_config& c) {
-  const int H = c.hidden;
-  return c.arch == SOMA_ARCH_LSTM && c.batch > 48 && c.batch <= 64 &&
-         (H == 128 || H == 256 || H == 512 || H == 704) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
+  const int H = rec_width(c);
+  if (c.arch == SOMA_ARCH_BODY || H % 64 != 0 || H > (c.arch == SOMA_ARCH_WIDE ? 512 : soma::kRecMaxH)) return false;
+  if (c.arch == SOMA_ARCH_LSTM && H < 128) return false;
+  const int64_t gin_slot_bytes = tile_rows(c) * 4 * H * int64_t(sizeof(float));
+  return c.batch > 32 && gin_slot_bytes < (int64_t(1) << 31) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
          !(c.flags & SOMA_FLAG_STAGED_RECURRENCE);
 }
-
-int xchg_tiles(int) { return soma::kXchgTiles; }
 
 // Groups the exchange recurrence can have at width H: 8 XCDs of at most 64
 // compute units, one block each, H / 32 blocks a group.
 int xchg_max_groups(int H) { return std::min(soma::kXchgMaxGroups, 8 * 64 / (H / 32)); }
 
-// Ring of two published steps per group: 16 NB rows x H, split (4 bytes a value).
+// Ring of two published steps per group: 64 rows x H, split (4 bytes a value).
 size_t xchg_ring_bytes(const soma_config& c) {
-  return size_t(xchg_max_groups(c.hidden)) * 2 * 16 * xchg_tiles(c.batch) * c.hidden * 4;
+  const int H = rec_width(c);
+  return size_t(xchg_max_groups(H)) * 2 * soma::kXchgRows * H * 4;
 }
 
 // Flags, then the per-compute-unit and per-rank placement counters.
 int xchg_counter_words() { return soma::kXchgMaxGroups * soma::kXchgFlagWords + soma::kXchgCuSlots + 8 * soma::kXchgMaxPerCu; }
+
+// Rows of one slot's gate inputs in the workspace (the larger of the two orders).
+int64_t gin_rows(const soma_config& c) {
+  return xchg_shape(c) ? tile_rows(c) : int64_t(c.seq_len - 1) * c.batch;
+}
+
+// Appends the exchange recurrence's ring and counters to a layout.
+void add_xchg(const soma_config& c, Layout* L, size_t* at) {
+  if (!xchg_shape(c)) return;
+  L->xch = *at;
+  L->xch_bytes = xchg_ring_bytes(c);
+  *at += round_up(L->xch_bytes + sizeof(unsigned) * xchg_counter_words());
+}
 
 Layout layout_for(const soma_config& c, int pc) {
   if (c.arch == SOMA_ARCH_BODY) return layout_for_body(c, pc);
@@ -287,12 +315,8 @@ Layout layout_for(const soma_config& c, int pc) {
   L.hpart = at; at += round_up(sizeof(float) * 2 * hslots * 2 * R);   // (m, s) per vocabulary half
   L.htgt = at; at += round_up(sizeof(float) * hslots * R);
   L.gin = at;
-  if (c.n_layers > 1) at += round_up(sizeof(float) * slots * R * 4 * H);
-  if (xchg_shape(c)) {
-    L.xch = at;
-    L.xch_bytes = xchg_ring_bytes(c);
-    at += round_up(L.xch_bytes + sizeof(unsigned) * xchg_counter_words());
-  }
+  if (c.n_layers > 1) at += round_up(sizeof(float) * slots * gin_rows(c) * 4 * H);
+  add_xchg(c, &L, &at);
   L.total = at;
   return L;
 }
@@ -783,31 +807,10 @@ const void* persist_kernel_for(int B, int H, int probe) {
   return probe == SOMA_PROBE_GAUSSIAN ? persist_kernel_for<false>(B, H) : persist_kernel_for<true>(B, H);
 }
 
-// The exchange recurrence for width H (xchg_shape) and the generator family
-// of probe law `probe`.
-template <bool kRad, bool kL1>
-const void* xchg_kernel_for(int nch) {
-  switch (nch) {
-    case 2: return reinterpret_cast<const void*>(&soma::k_rec_xchg<2, kRad, kL1>);
-    case 3: return reinterpret_cast<const void*>(&soma::k_rec_xchg<3, kRad, kL1>);
-    case 4: return reinterpret_cast<const void*>(&soma::k_rec_xchg<4, kRad, kL1>);
-    case 5: return reinterpret_cast<const void*>(&soma::k_rec_xchg<5, kRad, kL1>);
-    case 6: return reinterpret_cast<const void*>(&soma::k_rec_xchg<6, kRad, kL1>);
-    case 7: return reinterpret_cast<const void*>(&soma::k_rec_xchg<7, kRad, kL1>);
-    case 8: return reinterpret_cast<const void*>(&soma::k_rec_xchg<8, kRad, kL1>);
-    case 9: return reinterpret_cast<const void*>(&soma::k_rec_xchg<9, kRad, kL1>);
-    case 10: return reinterpret_cast<const void*>(&soma::k_rec_xchg<10, kRad, kL1>);
-    case 11: return reinterpret_cast<const void*>(&soma::k_rec_xchg<11, kRad, kL1>);
-    default: return nullptr;
-  }
-}
-
-// The instance for width H, the probe kind and the layer (layer 1 reads the
-// folded table).
-const void* xchg_kernel_for(int H, int probe, bool layer1) {
-  const bool rad = probe != SOMA_PROBE_GAUSSIAN;
-  if (layer1) return rad ? xchg_kernel_for<true, true>(H / 64) : xchg_kernel_for<false, true>(H / 64);
-  return rad ? xchg_kernel_for<true, false>(H / 64) : xchg_kernel_for<false, false>(H / 64);
+// The exchange recurrence's instance for a configuration and layer.
+const void* xchg_kernel(const soma_config& c, bool layer1) {
+  if (c.arch == SOMA_ARCH_WIDE) return soma::xchg_pre_kernel_for(rec_width(c));
+  return soma::xchg_kernel_for(c.hidden, c.probe != SOMA_PROBE_GAUSSIAN, layer1);
 }
 
 // Groups of the exchange recurrence (a multiple of 8, each on one XCD), or
@@ -816,9 +819,9 @@ const void* xchg_kernel_for(int H, int probe, bool layer1) {
 int xchg_groups(const soma_ctx* ctx) {
   const soma_config& c = ctx->cfg;
   if (!xchg_shape(c) || ctx->xchg_per_cu <= 0) return 0;
-  const int ut = c.hidden / 32;
+  const int ut = rec_width(c) / 32;
   const int groups = 8 * (ctx->xchg_per_cu * ctx->xchg_cus_per_xcd / ut);
-  return groups >= 8 && groups <= xchg_max_groups(c.hidden) ? groups : 0;
+  return groups >= 8 && groups <= xchg_max_groups(rec_width(c)) ? groups : 0;
 }
 
 // Its instantiation on pre-formed weights (the wide controls' body, d_p <= 512).
@@ -1010,6 +1013,37 @@ int launch_persist(const void* kernel, const Args& p, int blocks, int threads, h
   return SOMA_OK;
 }
 
+// One layer's recurrence through the exchange (xgroups = xchg_groups(ctx) > 0)
+// for `slots` slots of the pass.
+int launch_xchg(soma_ctx* ctx, const soma::FwdArgs& a, int xgroups, int slots, bool layer1, bool split_out,
+                hipStream_t st) {
+  const Layout& L = ctx->lay;
+  soma::XchgArgs p{};
+  p.a = a;
+  p.xh = reinterpret_cast<_Float16*>(ctx->ws + L.xch);
+  p.flag = reinterpret_cast<unsigned*>(ctx->ws + L.xch + L.xch_bytes);
+  p.cu_count = p.flag + soma::kXchgMaxGroups * soma::kXchgFlagWords;
+  p.rank_count = p.cu_count + soma::kXchgCuSlots;
+  p.err = a.err;
+  p.groups = xgroups;
+  p.cus_per_xcd = ctx->xchg_cus_per_xcd;
+  p.per_cu = ctx->xchg_per_cu;
+  p.bblocks = (ctx->cfg.batch + soma::kXchgRows - 1) / soma::kXchgRows;
+  p.jobs = slots * p.bblocks;
+  p.spin_limit = ctx->spin_limit;
+  p.split_out = split_out ? 1 : 0;
+  // Flags and placement counters restart at zero for every launch.
+  const int words = xchg_counter_words();
+  hipLaunchKernelGGL(soma::k_zero_u32, dim3((words + 255) / 256), dim3(256), 0, st, p.flag, words);
+  if (int rc = check_launch("k_zero_u32")) return rc;
+  const int blocks = ctx->xchg_per_cu * 8 * ctx->xchg_cus_per_xcd;
+  if (int rc = launch_persist(xchg_kernel(ctx->cfg, layer1), p, blocks, 512, st, unsigned(ctx->xchg_pad_lds)))
+    return rc;
+  ctx->rec_launches += 1;
+  ctx->xchg_launches += 1;
+  return SOMA_OK;
+}
+
 // The paper's body: one fused launch per pass (SOMA_ARCH_BODY).
 template <int DW, int D, bool kPert>
 void launch_body_t(const soma::BodyArgs& a, unsigned blocks, hipStream_t st) {
@@ -1073,6 +1107,8 @@ int launch_wide_mm(int epi, bool a_split, soma::MmArgs m, int slots, hipStream_t
     hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiGelu>), grid, block, 0, st, m);
   else if (epi == soma::kEpiAdd)
     hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiAdd>), grid, block, 0, st, m);
+  else if (epi == soma::kEpiGates)
+    hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiGates>), grid, block, 0, st, m);
   else
     hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiStore>), grid, block, 0, st, m);
   return check_launch("k_wide_mm");
@@ -1090,6 +1126,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   const soma::WideForm F = soma::wide_form_layout(dp, D);
   const int64_t mp = 4 * int64_t(dp) * dp;
   unsigned* err = reinterpret_cast<unsigned*>(ctx->ws + L.sync) + kMaxGroups;
+  const int xgroups = xchg_groups(ctx);
   const int groups = persistent_groups_h(ctx, slots, dp);
   if (groups <= 0) return fail(SOMA_EDEVICE, "the wide body needs the persistent recurrence (cooperative launch)");
 
@@ -1146,6 +1183,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   m.NS = NS;
   m.err = err;
   m.w_slot = F.total;
+  m.B = c.batch;
   // U = E P_in^T: the input projection of every byte value.
   m.A = ctx->head;
   m.a_slot = ctx->head_stride;
@@ -1171,10 +1209,10 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     m.a_slot = R * dp;
     m.W = blk;
     m.C = a.gin;
-    m.c_slot = R * 4 * dp;
+    m.c_slot = (xgroups > 0 ? tile_rows(c) : R) * 4 * dp;
     m.N = 4 * dp;
     m.K = dp;
-    if (int rc = launch_wide_mm(soma::kEpiStore, true, m, slots, st)) return rc;
+    if (int rc = launch_wide_mm(xgroups > 0 ? soma::kEpiGates : soma::kEpiStore, true, m, slots, st)) return rc;
     if (int rc = mark(ctx, kPhaseProj, st)) return rc;
     ++ctx->proj_launches;
     // the recurrence on the pre-formed R; h into the n buffer
@@ -1206,20 +1244,24 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     f.wpre = blk + mp;
     f.wpre_slot = F.total;
     f.ns = NS;
-    soma::PersistArgs p{};
-    p.a = f;
-    p.bar = reinterpret_cast<unsigned*>(ctx->ws + L.sync);
-    p.err = err;
-    p.groups = groups;
-    p.jobs = slots;
-    p.spin_limit = ctx->spin_limit;
-    hipLaunchKernelGGL(soma::k_zero_u32, dim3((groups + 255) / 256), dim3(256), 0, st, p.bar, groups);
-    if (int rc = check_launch("k_zero_u32")) return rc;
-    const int nw = soma::persist_waves(dp, c.batch);
-    const void* kern = persist_pre_kernel_for(c.batch, dp);
-    if (!kern) return fail(SOMA_ESHAPE, "no persistent recurrence for d_p = %d", dp);
-    if (int rc = launch_persist(kern, p, groups * (dp / (4 * nw)), 64 * nw, st)) return rc;
-    ctx->rec_launches += 1;
+    if (xgroups > 0) {
+      if (int rc = launch_xchg(ctx, f, xgroups, slots, false, false, st)) return rc;
+    } else {
+      soma::PersistArgs p{};
+      p.a = f;
+      p.bar = reinterpret_cast<unsigned*>(ctx->ws + L.sync);
+      p.err = err;
+      p.groups = groups;
+      p.jobs = slots;
+      p.spin_limit = ctx->spin_limit;
+      hipLaunchKernelGGL(soma::k_zero_u32, dim3((groups + 255) / 256), dim3(256), 0, st, p.bar, groups);
+      if (int rc = check_launch("k_zero_u32")) return rc;
+      const int nw = soma::persist_waves(dp, c.batch);
+      const void* kern = persist_pre_kernel_for(c.batch, dp);
+      if (!kern) return fail(SOMA_ESHAPE, "no persistent recurrence for d_p = %d", dp);
+      if (int rc = launch_persist(kern, p, groups * (dp / (4 * nw)), 64 * nw, st)) return rc;
+      ctx->rec_launches += 1;
+    }
     if (int rc = mark(ctx, kPhaseRec, st)) return rc;
     // x += h; n = LN(x); m = GELU(n U'^T); x += m V^T
     hipLaunchKernelGGL((soma::k_wide_ln<1>), ln_grid, dim3(256), 0, st, a);
@@ -1307,6 +1349,8 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
   a.layer = 0;
   a.in_l = c.embed;
   a.off_l = L.off_layer[0];
+  const int xgroups = kPert ? xchg_groups(ctx) : 0;
+  a.tiled = xgroups > 0 ? 1 : 0;   // every layer's recurrence is the exchange
   const bool emb_local = kPert && local_embedding(c);
   // One layer at H = 64 with the embedding in the block: the head and the
   // cross entropy run in the recurrence block too (no h in HBM, no head
@@ -1342,7 +1386,6 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       ++ctx->proj_launches;
     }
     const int groups = kPert ? persistent_groups(ctx, 2 * N * pcs) : 0;
-    const int xgroups = kPert ? xchg_groups(ctx) : 0;
     bool out_split = false;   // this layer's recurrence stores its h split
     if (kPert && local_recurrence(c)) {
       // H = 64: one block per job, h kept in the block between steps.
@@ -1351,32 +1394,10 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       if (int rc = launch_local(a, jobs, c.batch, c.probe, kx, fused_head, st)) return rc;
       ctx->rec_launches += 1;
     } else if (xgroups > 0) {
-      soma::XchgArgs p{};
-      p.a = a;
-      p.xh = reinterpret_cast<_Float16*>(ctx->ws + L.xch);
-      p.flag = reinterpret_cast<unsigned*>(ctx->ws + L.xch + L.xch_bytes);
-      p.cu_count = p.flag + soma::kXchgMaxGroups * soma::kXchgFlagWords;
-      p.rank_count = p.cu_count + soma::kXchgCuSlots;
-      p.err = a.err;
-      p.groups = xgroups;
-      p.cus_per_xcd = ctx->xchg_cus_per_xcd;
-      p.per_cu = ctx->xchg_per_cu;
-      p.jobs = 2 * N * pcs;   // (expert, direction, sign)
-      p.spin_limit = ctx->spin_limit;
-      // Flags and placement counters restart at zero for every launch.
-      const int words = xchg_counter_words();
-      hipLaunchKernelGGL(soma::k_zero_u32, dim3((words + 255) / 256), dim3(256), 0, st, p.flag, words);
-      if (int rc = check_launch("k_zero_u32")) return rc;
-      const int blocks = ctx->xchg_per_cu * 8 * ctx->xchg_cus_per_xcd;
       // The next layer's projection reads this layer's h pre-split (k_proj_dma).
-      p.split_out = l + 1 < c.n_layers && stream_weights(c) && proj_dma_width(H) && c.batch % 16 == 0 &&
-                    !(c.flags & SOMA_FLAG_FP32_SEQUENCE) ? 1 : 0;
-      out_split = p.split_out != 0;
-      if (int rc = launch_persist(xchg_kernel_for(H, c.probe, l == 0), p, blocks, 512, st,
-                                  unsigned(ctx->xchg_pad_lds)))
-        return rc;
-      ctx->rec_launches += 1;
-      ctx->xchg_launches += 1;
+      out_split = l + 1 < c.n_layers && stream_weights(c) && proj_dma_width(H) && c.batch % 16 == 0 &&
+                  !(c.flags & SOMA_FLAG_FP32_SEQUENCE);
+      if (int rc = launch_xchg(ctx, a, xgroups, 2 * N * pcs, l == 0, out_split, st)) return rc;
     } else if (groups > 0) {
       soma::PersistArgs p{};
       p.a = a;
@@ -1470,9 +1491,7 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
     // The exchange recurrence: one block per compute unit (unused dynamic LDS
     // caps the occupancy where more would fit: every compute unit must hold
     // exactly one block for the placement), compute units per XCD (8 XCDs,
-    // blocks dealt to them round-robin).  A launch that placed two of its
-    // blocks on each compute unit faulted the device, with no cause found
-    // in the kernel's indexing; that placement stays off.
+    // blocks dealt to them round-robin).
     // Both instances (layer 1, deeper layers) must take the same geometry.
     int dev = 0, coop = 0, cus = 0, lds_cu = 0;
     const bool dev_ok = hipGetDevice(&dev) == hipSuccess &&
@@ -1483,7 +1502,7 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
                         coop && cus % 8 == 0 && cus / 8 <= 64;
     int pad_of[2] = {-1, -1};
     for (int l1 = 0; l1 < 2 && dev_ok; ++l1) {
-      const void* kern = xchg_kernel_for(cfg->hidden, cfg->probe, l1 == 1);
+      const void* kern = xchg_kernel(*cfg, l1 == 1);
       hipFuncAttributes fa{};
       int occ = 0;
       if (!kern || hipFuncGetAttributes(&fa, kern) != hipSuccess ||
@@ -2072,9 +2091,14 @@ int soma_box_muller(const uint32_t* wa, const uint32_t* wb, float* za, float* zb
 namespace {
 
 constexpr size_t kStaticScratchBytes = size_t(32) << 20;
+// What the exchange recurrence takes on top: its ring and counters (at most
+// 8 MiB + 0.3 MiB: every width's groups together publish 64 rows x 2 steps for
+// 512 compute units) and the gate inputs' whole row tiles (33 sequences take
+// the place of 48: less than half of 32 MiB more).
+constexpr size_t kExchangeScratchBytes = size_t(24) << 20;
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kExchangeScratchBytes];
 
 std::mutex g_scratch_mu;
 char* g_scratch_ptr[kMaxDevices] = {};
@@ -2098,11 +2122,23 @@ int scratch_address(char** out) {
 }
 
 // The largest direction chunk whose workspace fits `budget` bytes (the
-// configured chunk if one is set), or 0 if none does.
+// configured chunk if one is set), or 0 if none does.  The limit holds shapes
+// to what they need on the staged recurrence; the exchange's area lies beyond
+// it, except for the batches and widths that have always counted it.
+size_t scratch_need(const soma_config& c, int pc) {
+  const Layout L = layout_for(c, pc);
+  const int H = c.hidden;
+  if (L.xch_bytes == 0) return L.total;
+  const bool counted = c.batch > 48 && c.batch <= 64 && (H == 128 || H == 256 || H == 512 || H == 704);
+  const size_t per_row = c.n_layers > 1 ? sizeof(float) * c.n_experts * size_t(pc) * 2 * 4 * H : 0;
+  const size_t padding = round_up(per_row * tile_rows(c)) - round_up(per_row * (c.seq_len - 1) * c.batch);
+  return (counted ? L.total : L.xch) - padding;   // the area ends the layout
+}
+
 int chunk_within(const soma_config& c, size_t budget) {
-  if (c.pair_chunk > 0) return layout_for(c, c.pair_chunk).total <= budget ? c.pair_chunk : 0;
+  if (c.pair_chunk > 0) return scratch_need(c, c.pair_chunk) <= budget ? c.pair_chunk : 0;
   for (int pc = dirs(c); pc >= 1; --pc)
-    if (layout_for(c, pc).total <= budget) return pc;
+    if (scratch_need(c, pc) <= budget) return pc;
   return 0;
 }
 
@@ -2115,11 +2151,11 @@ extern "C" int soma_spsa_step_noalloc(const soma_config* cfg, float* theta, cons
   const int pc = chunk_within(*cfg, kStaticScratchBytes);
   if (pc == 0)
     return fail(SOMA_ESHAPE, "this shape needs %zu bytes of scratch per direction; the static scratch holds %zu",
-                layout_for(*cfg, 1).total, kStaticScratchBytes);
+                scratch_need(*cfg, 1), kStaticScratchBytes);
   char* ws = nullptr;
   if (int rc = scratch_address(&ws)) return rc;
   const Layout L = layout_for(*cfg, pc);
   soma_ctx ctx;   // host stack: its event pool stays empty (no phase timing here)
-  init_ctx(&ctx, *cfg, L, ws, kStaticScratchBytes);
+  init_ctx(&ctx, *cfg, L, ws, kStaticScratchBytes + kExchangeScratchBytes);
   return soma_spsa_step(&ctx, theta, seeds, step, eps, lr, bytes, losses, stream);
 }

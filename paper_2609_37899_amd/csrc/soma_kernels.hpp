@@ -15,7 +15,15 @@
 //   part  [slot][row tiles]      per-tile sums of cross entropy (fp64)
 // The last axis of U and gin is gate-interleaved: column 4u + g holds gate g
 // (i, f, g, o) of unit u, so that one MFMA output lane holds the four gates
-// of one unit.
+// of one unit.  For the exchange recurrence (FwdArgs::tiled) both are cut
+// into the pieces its blocks (32 units) read:
+//   U     [slot][H/32][256][32 units][4]
+//   gin   [slot][T-1][ceil(B/16)][H/32][8][64 lanes][4]: per row tile of 16
+//         sequences and block 8 KiB, 1 KiB for each quad of units in the
+//         order of an MFMA result block (lane 16 lg + lr: unit lg, row lr)
+// With whole rows of 4H floats a load of 16 rows is 16 lines 16 H bytes apart,
+// a multiple of the caches' channel interleave at most widths: one channel
+// serves them all.
 //
 // Matrix cores: V_MFMA_F32_16X16X4_F32.  For A (16 x 4), B (4 x 16) and
 // D (16 x 16), lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and
@@ -242,6 +250,7 @@ struct FwdArgs {
   int N, E, H, B, T, PC;  // PC = slot stride in directions
   int pcs;                // directions in this pass (grid extent)
   int j0;                 // first direction of the chunk
+  int tiled;              // U and gin in the tiled order of the exchange recurrence
   int layer;              // current layer (0-based)
   int in_l;               // input width of the current layer
   int t;                  // time step (rec kernel)
@@ -347,7 +356,9 @@ __global__ __launch_bounds__(kThreads) void k_fold(FwdArgs a) {
 #pragma unroll
     for (int nb = 0; nb < 4; ++nb) {
       const int v = v0 + nb * 16 + lr;
-      float* dst = a.U + (slot * kVocab + v) * (4 * static_cast<int64_t>(H)) + p;
+      float* dst = a.U + slot * kVocab * (4 * static_cast<int64_t>(H)) +
+                   (a.tiled ? (static_cast<int64_t>(p >> 7) * kVocab + v) * 128 + (p & 127)
+                            : v * (4 * static_cast<int64_t>(H)) + p);
       *reinterpret_cast<float4*>(dst) =
           make_float4(acc[s][nb][0], acc[s][nb][1], acc[s][nb][2], acc[s][nb][3]);
     }
@@ -491,6 +502,11 @@ __global__ __launch_bounds__(kThreads) void k_proj(FwdArgs a) {
       const int64_t row = r0 + nb * 16 + lr;
       if (row < R) {
         float* dst = a.gin + ((slot0 + s) * R + row) * (4 * static_cast<int64_t>(H)) + p;
+        if (a.tiled) {                          // unit p / 4 of sequence b of step t
+          const int64_t t = row / a.B, b = row % a.B, RT = (a.B + 15) / 16;
+          dst = a.gin + (slot0 + s) * (a.T - 1) * RT * 64 * H +
+                (((t * RT + b / 16) * (H / 32) + (p >> 7)) * 8 + ((p >> 4) & 7)) * 256 + (b % 16 + 16 * ((p >> 2) & 3)) * 4;
+        }
         *reinterpret_cast<float4*>(dst) =
             make_float4(acc[0][s][nb][0], acc[0][s][nb][1], acc[0][s][nb][2], acc[0][s][nb][3]);
       }
@@ -1275,78 +1291,19 @@ __global__ __launch_bounds__(64 * NW, 1) void k_rec_persist(PersistArgs p) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// Persistent recurrence with a pipelined split exchange (k_rec_xchg): the
-// per-step arithmetic of k_rec_persist -- G_t = G_in,t + h_{t-1} W_h+-^T on
-// the fp16 matrix cores from split operands, the cell update in the lane
-// that holds a unit's four gates -- organised so that the exchange of h
-// between the blocks of a group overlaps the products.
-//
-//  * The batch's row tiles (16 sequences each) are independent recurrences
-//    that share the block's resident weights.  A block runs sub-steps
-//    s = (t, k) in the order t, then tile k: the products of tile k at step
-//    t need only tile k's h_{t-1}, published NB sub-steps earlier, so its
-//    exchange is hidden behind the products of the other tiles (NB >= 4).
-//  * Each block publishes its 32 units of h_t of a tile (one 32-wide K
-//    chunk) already split into fp16 hi and lo parts, in one of two layouts
-//    of the chunk's 2 KiB.  Fragment order (H <= 512): per part (hi, lo) 64
-//    lanes x 8 halves, lane (lr, lg) holding row lr, columns 8 lg .. + 7,
-//    read by the products as they are; the block transposes h_t through
-//    LDS (one more block barrier) and two waves store whole lines.  Words
-//    (H >= 640): per wave and row one 16-byte word, the four hi parts then
-//    the four lo parts, word (w, r) at index 64 (w & 1) + 16 (w >> 1) + r,
-//    stored straight from the lanes of the cell update (a wave holds 4 units
-//    of each row; three lane swaps bring them together); lane (lr, lg) reads
-//    the words at indices lane and 64 + lane and takes its fragments from
-//    them by register moves.  Either way every 128-byte line is written by
-//    one wave: halves of one word stored by two waves (device coherent) now
-//    and then left a half two steps old.  A group keeps two steps per tile
-//    (parity t mod 2) in L2.  h_t is also written to the layer's hseq rows
-//    for the kernels that read the whole sequence: in fp32, or (split_out:
-//    fragment order, B = 64, where the next layer's projection is
-//    k_proj_dma) as the same split words, in 1 KiB blocks [16-row tile][hi,
-//    lo][32-wide k chunk], word 16 lg + lr holding row lr, k 8 lg .. + 7.
-//  * The tile's h_{t-1} reaches LDS by DMA (buffer_load_dwordx4 ... lds):
-//    each 1 KiB block lands unchanged -- no staging registers, vector
-//    instructions or LDS stores.  The DMA of sub-step s + 2 is issued after
-//    a block barrier of sub-step s, into the LDS buffer the products of
-//    sub-step s have released (two buffers).
-//  * Arrival is a per-(tile, block) flag word holding the steps published.
-//    A sub-step's stores are acknowledged during the next sub-step's
-//    products (one vmcnt(0) per sub-step, after the products: loads and
-//    stores share the counter and may complete out of order, so only a full
-//    wait is sound), and the flag is raised right behind the barrier that
-//    follows; the flags needed for the DMA of sub-step s + 2 (raised a
-//    sub-step earlier) are read with one load issued halfway through the
-//    products of sub-step s and checked after them.
-//  * The gate inputs of a tile's next step go out as early as the wait
-//    allows: at layer 1 (rows of the folded table gathered by byte value,
-//    often cache misses) right after the wait, for the next sub-step's
-//    tile; at deeper layers (a stream of the time-parallel gate inputs)
-//    right after the cell update, which measured faster there.
-//
-// Every wait is bounded: a wave that polls longer than the spin limit, or
-// that sees the step's abort flag, sets the flag and stops waiting; every
-// wave then runs to the end without waiting (on stale data), so the grid
-// drains, and the losses read NaN.  A block of 8 waves owns 128 gate rows
-// (32 units); a group of H / 32 blocks sits on one XCD; one block per
-// compute unit, claimed at start from the compute unit it runs on.
-//
-// The LDS DMA is issued through inline assembly: the compiler assumes that a
-// pending LDS DMA may alias every later LDS read and would wait for it
-// before each fragment read.  Its completion is covered by the sub-step's
-// vmcnt(0) and the block barrier that follows.
-// ---------------------------------------------------------------------------
+// The exchange recurrence (soma_xchg.hpp): constants and arguments, and the
+// LDS DMA it shares with the projection.
 constexpr int kXchgMaxGroups = 256;    // groups of one launch (flags in the workspace)
 constexpr int kXchgFlagWords = 256;    // flag words per group: [tile][block], H / 32 <= 64 blocks
 constexpr int kXchgCuSlots = 8 * 64;   // blocks-per-compute-unit counters: (XCD, shader engine, CU)
 constexpr int kXchgMaxPerCu = 4;
-constexpr int kXchgTiles = 4;          // row tiles the pipeline needs: B > 48
+constexpr int kXchgTiles = 4;          // row tiles of a job
+constexpr int kXchgRows = 16 * kXchgTiles;
 constexpr unsigned kAbortPlace = 4u;   // a block found no (group, tile) to claim
 
 struct XchgArgs {
   FwdArgs a;
-  _Float16* xh;          // [groups][2][NB][H/32][wave & 1][wave >> 1][16 rows][4 hi + 4 lo] published h, split
+  _Float16* xh;          // [groups][2][tiles][H/32][hi, lo][64 words][8] published h, split
   unsigned* flag;        // [groups][kXchgFlagWords] steps published per (tile, block), over all jobs
   unsigned* cu_count;    // [kXchgCuSlots] blocks started per compute unit (zero at launch)
   unsigned* rank_count;  // [8][kXchgMaxPerCu] blocks claimed per (XCD, rank on the CU) (zero at launch)
@@ -1354,7 +1311,8 @@ struct XchgArgs {
   int groups;            // 8 * groups per XCD
   int cus_per_xcd;       // compute units per XCD
   int per_cu;            // blocks per compute unit of the launch
-  int jobs;              // N * directions in this pass * 2 signs
+  int jobs;              // slots of this pass (N * directions * signs) * bblocks
+  int bblocks;           // 64-sequence blocks of the batch
   unsigned spin_limit;   // polls per wait before giving up
   int split_out;         // store the layer's h to hseq split, in fragment-order blocks (for k_proj_dma)
 };
@@ -1387,328 +1345,6 @@ __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t soff, 
                :
                : "v"(voff), "s"(rsrc), "s"(soff), "{m0}"(lds)
                : "memory");
-}
-
-// kL1: the layer reads its inputs from the folded table by byte value (layer
-// 1) rather than from the time-parallel gate inputs; a template parameter so
-// that each instance loads its inputs on one path (the compiler would
-// otherwise merge the two paths' pending loads and wait for all of them).
-template <int NCH, bool kRad, bool kL1>
-__global__ __launch_bounds__(512) void k_rec_xchg(XchgArgs p) {
-  constexpr int NW = 8;                                 // waves: 128 gate rows, 32 units (one K chunk of h)
-  constexpr int NU = 4 * NW;
-  constexpr int NB = kXchgTiles;                        // row tiles of 16 sequences
-  constexpr int KC = 2 * NCH;                           // 32-wide k chunks: H = 64 NCH
-  constexpr int FRAG = 512;                             // halves per 1 KiB block (half a chunk of a tile)
-  constexpr int TBUF = KC * 2 * FRAG;                   // halves of one tile's h in LDS
-  constexpr int XTILE = KC * 2 * FRAG;                  // halves per published (step, tile)
-  constexpr int XSLOT = 2 * NB * XTILE;                 // halves per group: parity x tile
-  constexpr int ZW = 128;                               // probe piece: 128 rows x (ZW + 8) floats
-  constexpr int ZS_BYTES = 16 * NW * (ZW + 8) * 4;
-  constexpr int RING_BYTES = 2 * TBUF * 2;
-  constexpr int LDS_BYTES = RING_BYTES > ZS_BYTES ? RING_BYTES : ZS_BYTES;
-  // Layout of the published h: 16-byte words per (wave, row) at H >= 640,
-  // published straight from the cell lanes (no LDS transpose, no second
-  // block barrier; measured 12% faster at H = 704, where the compiler also
-  // spills fewer registers: 13 against 25); else the MFMA fragment order,
-  // transposed through LDS, whose fragments need no register moves between
-  // the LDS reads and the products (faster at H = 512).
-  constexpr bool kWords = NCH >= 10;
-  constexpr int NBLK = 2 * KC;                          // 1 KiB blocks per tile: (chunk, half)
-  constexpr int BPW = (NBLK + NW - 1) / NW;             // of them per wave (the last ones may be short)
-  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_BYTES];
-  constexpr int HTLD = NU + 4;                          // LDS row of the h_t tile (float4-aligned)
-  __shared__ __attribute__((aligned(16))) float ht[kWords ? 4 : 16 * HTLD];
-  __shared__ int role[2];
-  _Float16* ring = reinterpret_cast<_Float16*>(lds);
-  const FwdArgs& a = p.a;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  const int H = a.H, B = a.B, T = a.T, in = a.in_l;
-  const int UT = H / NU;                                // blocks per group
-
-  // Claim (group, unit tile): rank r = how many blocks started on this
-  // compute unit before this one, i = how many blocks of rank r on this XCD
-  // claimed before; position r * cus_per_xcd + i of the XCD's per_cu *
-  // cus_per_xcd blocks, UT consecutive positions per group, positions past
-  // the XCD's whole groups idle.
-  if (threadIdx.x == 0) {
-    const unsigned hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);         // HW_ID
-    const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15;  // XCC_ID
-    const unsigned cu = ((hw >> 13) & 3) * 16 + ((hw >> 8) & 15);          // shader engine, compute unit
-    int grp = -2, tile = 0;                             // -2: unplaced (an error), -1: idle
-    if (xcc < 8) {
-      const unsigned r = __hip_atomic_fetch_add(&p.cu_count[xcc * 64 + cu], 1u, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-      if (r < static_cast<unsigned>(p.per_cu)) {
-        const unsigned i = __hip_atomic_fetch_add(&p.rank_count[xcc * kXchgMaxPerCu + r], 1u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-        if (i < static_cast<unsigned>(p.cus_per_xcd)) {
-          const int pos = static_cast<int>(r) * p.cus_per_xcd + static_cast<int>(i);
-          grp = pos < (p.groups / 8) * UT ? (pos / UT) * 8 + static_cast<int>(xcc) : -1;
-          tile = pos % UT;
-        }
-      }
-    }
-    if (grp == -2) __hip_atomic_fetch_or(p.err, kAbortPlace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    role[0] = grp;
-    role[1] = tile;
-  }
-  __syncthreads();
-  const int grp = role[0], utile = role[1];
-  if (grp < 0) return;
-  unsigned* const flags = p.flag + grp * kXchgFlagWords;   // [tile][block]
-  const uint32_t xbytes = static_cast<uint32_t>(p.groups) * XSLOT * 2u;
-  const i32x4 xrs = buffer_words(p.xh, xbytes);            // the same buffer for the DMA (scalar words)
-  const __amdgpu_buffer_rsrc_t xbuf = buffer_of(p.xh, xbytes);
-  const int unit = utile * NU + wave * 4 + lg;          // output unit of this lane
-  const int64_t R = static_cast<int64_t>(T - 1) * B;
-  const int64_t H4 = 4 * static_cast<int64_t>(H);
-  const uint32_t slot_bytes = static_cast<uint32_t>(R * H * sizeof(float));   // < 2^31 (host check)
-  const int S = (T - 1) * NB;                           // sub-steps of a job
-  bool failed = false;                                  // this wave stopped waiting (abort)
-
-  // Poll until every block of the group has published `target` steps of
-  // tile k (flag words [k][0 .. UT)), or give up.  Every wave polls for
-  // itself; after an abort nothing waits any more.  One load per poll: lane
-  // 63 reads the abort flag, the others their flag word, so no load of the
-  // loop is left outstanding when it exits (the compiler would otherwise
-  // wait for all memory accesses before the register is reused).
-  auto ready = [&](unsigned target, unsigned v) { return __builtin_amdgcn_ballot_w64(lane < UT && v < target) == 0; };
-  auto wait_flags = [&](int k, unsigned target) {
-    unsigned polls = 0;
-    const unsigned* addr = lane == 63 ? p.err : flags + k * 64 + lane;
-    while (!failed) {
-      const unsigned v = __hip_atomic_load(addr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned f = __builtin_amdgcn_readlane(v, 63);
-      if (ready(target, v)) break;
-      if (f != 0u || ++polls > p.spin_limit) {
-        if (lane == 0) __hip_atomic_fetch_or(p.err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        failed = true;
-      } else {
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  };
-
-  unsigned base = 0;                                    // steps of every tile published in earlier jobs
-  for (int job = grp; job < p.jobs; job += p.groups, base += static_cast<unsigned>(T - 1)) {
-    const int sg = job & 1, pj = job >> 1;
-    const int e = pj / a.pcs, jl = pj % a.pcs;
-    const float* th = a.theta + static_cast<int64_t>(e) * a.d;
-    const uint2 key = stream_key(a.seeds[e], a.step);
-    const uint32_t pair = static_cast<uint32_t>(a.j0 + jl), step_lo = static_cast<uint32_t>(a.step);
-    const int64_t slot = (static_cast<int64_t>(e) * a.PC + jl) * 2 + sg;
-    const float seps = sg == 0 ? eps_of(a, e, kGroupLstm) : -eps_of(a, e, kGroupLstm);
-    const __amdgpu_buffer_rsrc_t hbuf = buffer_of(a.hseq + slot * R * H, slot_bytes);
-    const __amdgpu_buffer_rsrc_t gbuf =
-        kL1 ? buffer_of(a.U + slot * kVocab * H4, static_cast<uint32_t>(kVocab * H4 * sizeof(float)))
-                     : buffer_of(a.gin + slot * R * H4, static_cast<uint32_t>(R * H4 * sizeof(float)));
-    const __amdgpu_buffer_rsrc_t bbuf = buffer_of(bytes_of(a, e, jl), static_cast<uint32_t>(B * T));
-
-    // The ring slots this job writes were read in the previous job: every
-    // block must have finished it (its last publication of every tile).
-    if (base > 0) {
-      for (int k = 0; k < NB; ++k) wait_flags(k, base);
-    }
-    // Perturbed recurrent weights of this lane's gate row, split, for the
-    // whole sequence (the probe scratch overlays the LDS ring; the barriers
-    // inside order it after the previous job's last fragment reads).
-    uint4 wh[KC], wl[KC];
-    resident_weights_split<KC, true, kRad, ZW, 16 * NW>(wh, wl, reinterpret_cast<float*>(lds), th, a.off_l, in + H,
-                                                        in, H, utile * 16 * NW, a.probe, key, pair, step_lo, seps,
-                                                        p.err);
-    float cs[NB];
-    int vb[NB];                                         // layer 1: byte of the next step of each tile
-    float4 gi[NB];                                      // gate inputs of each tile's next step
-    const uint32_t byte_lane = static_cast<uint32_t>(lr * T);
-    const uint32_t gi_lane = static_cast<uint32_t>((lr * 4 * H + 4 * unit) * 4);
-    // Gate inputs of (step tt, tile k) into gi[k]; layer 1 reads its folded
-    // inputs by byte value and fetches the byte of step tt + 1 along.
-    auto load_inputs = [&](int tt, int k) {
-      if constexpr (kL1) {
-        gi[k] = buffer_load_f4<0>(gbuf, static_cast<uint32_t>((vb[k] * 4 * H + 4 * unit) * 4));
-        vb[k] = __builtin_amdgcn_raw_buffer_load_b8(bbuf, byte_lane, static_cast<uint32_t>(k * 16 * T + tt + 1), 0);
-      } else {
-        gi[k] = buffer_load_f4s<0>(gbuf, gi_lane, static_cast<uint32_t>((tt * B + k * 16) * 4 * H * 4));
-      }
-    };
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      cs[k] = 0.0f;
-      vb[k] = kL1 ? __builtin_amdgcn_raw_buffer_load_b8(bbuf, byte_lane, static_cast<uint32_t>(k * 16 * T), 0)
-                           : 0;
-    }
-    if constexpr (kL1) {
-      load_inputs(0, 0);                                // the others go out one sub-step ahead
-    } else {
-#pragma unroll
-      for (int k = 0; k < NB; ++k) load_inputs(0, k);
-    }
-
-    // Sub-step s = (t, k) reads tile k's h_{t-1} (published by every block
-    // at sub-step s - NB) from LDS buffer s & 1, filled by DMA issued in
-    // sub-step s - 2.
-    auto issue = [&](int s) {
-      const int t = s / NB, k = s % NB;
-      const uint32_t src = static_cast<uint32_t>((grp * XSLOT + (((t - 1) & 1) * NB + k) * XTILE) * 2);
-      const uint32_t dst = lds_address(ring + (s & 1) * TBUF);
-#pragma unroll
-      for (int i = 0; i < BPW; ++i) {
-        const int b = wave + NW * i;                    // chunk b / 2, half b % 2
-        if (NBLK % NW == 0 || b < NBLK)                 // wave-uniform
-          dma16(xrs, static_cast<uint32_t>(lane * 16), src + static_cast<uint32_t>(b * FRAG * 2),
-                dst + static_cast<uint32_t>(b * FRAG * 2));
-      }
-    };
-    for (int t = 0; t + 1 < T; ++t) {
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        const int s = t * NB + k;
-        // DMA(s + 2) is issued after this sub-step's barrier; its flags, read
-        // halfway through the products, are checked once they are done.
-        const int s2 = s + 2, t2 = s2 / NB;
-        const int k2 = (k + 2) % NB;
-        const bool need2 = s2 < S && t2 >= 1;
-        unsigned v2 = 0;
-        f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (t >= 1) {
-          // buffer s & 1 (NB is even): each read is one contiguous KiB over
-          // the wave's lanes
-          const _Float16* bsrc = ring + (k & 1) * TBUF + lane * 8;
-#pragma unroll
-          for (int c = 0; c < KC; ++c) {
-            if (c == KC / 2 && need2)
-              v2 = __hip_atomic_load(flags + k2 * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint4 w0 = *reinterpret_cast<const uint4*>(bsrc + c * 2 * FRAG);
-            const uint4 w1 = *reinterpret_cast<const uint4*>(bsrc + c * 2 * FRAG + FRAG);
-            // Words: lane (lr, lg) takes those of waves 2 lg and 2 lg + 1 for
-            // its row (K 8 lg .. + 3 and 8 lg + 4 .. + 7); fragments: as read.
-            const uint4 bh = kWords ? make_uint4(w0.x, w0.y, w1.x, w1.y) : w0;
-            const uint4 bl = kWords ? make_uint4(w0.z, w0.w, w1.z, w1.w) : w1;
-            const h8 AH = __builtin_bit_cast(h8, wh[c]), AL = __builtin_bit_cast(h8, wl[c]);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(AL, __builtin_bit_cast(h8, bh), acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(AH, __builtin_bit_cast(h8, bl), acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(AH, __builtin_bit_cast(h8, bh), acc, 0, 0, 0);
-          }
-        } else if (need2) {
-          v2 = __hip_atomic_load(flags + k2 * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        // Every memory access of this wave has completed: the stores of
-        // sub-step s - 1, the DMA of sub-step s + 1, the flag load, the inputs.
-        // (Loads and stores share the counter and may complete out of order,
-        // so only a full wait is sound here.)
-        wait_vmem();
-        // Layer 1: the inputs of the next sub-step's tile, as early as they
-        // can go (the folded table's rows are gathered by byte value and often
-        // miss the cache; the next wait covers them, a whole sub-step on).
-        if constexpr (kL1) {
-          if (s + 1 < S) load_inputs(k + 1 < NB ? t : t + 1, (k + 1) % NB);
-        }
-        __syncthreads();
-        // Raise the flag of the previous publication (tile k - 1 at step t, or
-        // the last tile at step t - 1): every wave's stores of it completed
-        // before the barrier.
-        if (threadIdx.x == 0 && s > 0) {
-          const int kp = (k + NB - 1) % NB;
-          const unsigned vp = base + static_cast<unsigned>(k == 0 ? t : t + 1);
-          __hip_atomic_store(flags + kp * 64 + utile, vp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (need2 && !ready(base + t2, v2)) wait_flags(k2, base + t2);
-        // Every wave's products of this sub-step are done: its LDS buffer
-        // takes the DMA of sub-step s + 2.
-        if (kWords && need2) issue(s2);
-        float h;
-        {
-          const float4 g = gi[k];
-          lstm_cell(acc[0] + g.x, acc[1] + g.y, acc[2] + g.z, acc[3] + g.w, cs[k], h);
-        }
-        // Deeper layers: the tile's inputs of the next step, streamed from
-        // the gate inputs (past the last step they read zeros past the
-        // buffer); issued here they cost less than right after the wait.
-        if constexpr (!kL1) load_inputs(t + 1, k);
-        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-        if constexpr (kWords) {
-          // Publish h_t of tile k straight from the cell lanes.  Lane (lr, lg)
-          // holds unit 4 wave + lg of row lr; the swaps give every lane of
-          // the row all four units.  Lane group 0 stores the row's word (the
-          // four hi parts, then the four lo parts), lane group 2 the four
-          // fp32 values to the layer's sequence when the row is inside the
-          // batch.  Every 128-byte line of the ring is written by one wave.
-          const auto p16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false, false);
-          const auto qa = __builtin_amdgcn_permlane32_swap(p16[0], p16[0], false, false);   // units 0, 2
-          const auto qb = __builtin_amdgcn_permlane32_swap(p16[1], p16[1], false, false);   // units 1, 3
-          const float4 hv = make_float4(__uint_as_float(qa[0]), __uint_as_float(qb[0]), __uint_as_float(qa[1]),
-                                        __uint_as_float(qb[1]));
-          if (lg == 0) {
-            uint2 hi, lo;
-            split4(hv, hi, lo);
-            const uint32_t off = static_cast<uint32_t>((grp * XSLOT + ((t & 1) * NB + k) * XTILE + utile * 2 * FRAG +
-                                                        (wave & 1) * FRAG + (16 * (wave >> 1) + lr) * 8) * 2);
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{hi.x, hi.y, lo.x, lo.y}, xbuf, off, 0, kCoherent);
-          } else if (lg == 2 && k * 16 + lr < B) {
-            const uint32_t off = static_cast<uint32_t>(((t * B + k * 16 + lr) * H + utile * NU + 4 * wave) * 4);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), hbuf, off, 0, 0);
-          }
-        } else {
-          // Fragment order: h_t of the tile is transposed through LDS, then
-          // threads 0..127 (part, word, row) split 8 units of one row into one
-          // fragment word, each wave storing whole lines; threads 128..255
-          // (row, quarter of 4 units) store the fp32 rows of the tile inside
-          // the batch.  (Halves of one word stored by two waves, device
-          // coherent, now and then left a half two steps old.)
-          ht[lr * HTLD + wave * 4 + lg] = h;
-          __syncthreads();
-          if (need2) issue(s2);
-          const int tid = threadIdx.x;
-          if (tid < 128) {
-            const int rr = tid & 15, hw = (tid >> 4) & 3, part = tid >> 6;
-            const float* srcw = &ht[rr * HTLD + 8 * hw];
-            uint4 hi, lo;
-            split8v(*reinterpret_cast<const float4*>(srcw), *reinterpret_cast<const float4*>(srcw + 4), hi, lo);
-            const uint4 v = part ? lo : hi;
-            const uint32_t off = static_cast<uint32_t>(
-                (grp * XSLOT + ((t & 1) * NB + k) * XTILE + (utile * 2 + part) * FRAG + (16 * hw + rr) * 8) * 2);
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, xbuf, off, 0, kCoherent);
-          } else if (tid < 256) {
-            if (p.split_out) {
-              // The same words as the exchange's, into the sequence's
-              // fragment-order layout: 1 KiB block (row tile, part, k chunk
-              // = this block's units), word 16 hw + rr.  (B % 16 == 0, so a
-              // tile of the batch is one row tile of the sequence.)  16-byte
-              // stores: a version with two 8-byte stores per thread (whose
-              // data registers the next instruction rewrote) left non-finite
-              // values under the Rademacher laws at H = 128; its cause was
-              // not established.
-              const int u = tid - 128, rr = u & 15, hw = (u >> 4) & 3, part = u >> 6;
-              const float* srcw = &ht[rr * HTLD + 8 * hw];
-              uint4 hi, lo;
-              split8v(*reinterpret_cast<const float4*>(srcw), *reinterpret_cast<const float4*>(srcw + 4), hi, lo);
-              const uint4 v = part ? lo : hi;
-              const int rt = (t * B) / 16 + k;
-              __builtin_amdgcn_raw_buffer_store_b128(
-                  u32x4{v.x, v.y, v.z, v.w}, hbuf,
-                  static_cast<uint32_t>((((rt * 2 + part) * KC + utile) * FRAG + (16 * hw + rr) * 8) * 2), 0, 0);
-            } else {
-              const int n = (tid - 128) >> 3, c4 = tid & 7, row = k * 16 + n;
-              if (row < B) {
-                const float4 v = *reinterpret_cast<const float4*>(&ht[n * HTLD + 4 * c4]);
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    __builtin_bit_cast(u32x4, v), hbuf,
-                    static_cast<uint32_t>(((t * B + row) * H + utile * NU + 4 * c4) * 4), 0, 0);
-              }
-            }
-          }
-        }
-      }
-    }
-    // The job's last publication (tile NB - 1 at step T - 2).
-    wait_vmem();
-    __syncthreads();
-    if (threadIdx.x == 0)
-      __hip_atomic_store(flags + (NB - 1) * 64 + utile, base + static_cast<unsigned>(T - 1), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2245,8 +1881,10 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_stream(
   // 32-bit offsets: R 4H floats < 2^31 bytes (host check).
   const __amdgpu_buffer_rsrc_t hbuf =
       buffer_of(a.hseq + slot * R * H, static_cast<uint32_t>(static_cast<int64_t>(R) * H * sizeof(float)));
+  const int RT = (B + 15) / 16;               // row tiles of a time step (tiled gate inputs)
+  const int64_t gin_rows = a.tiled ? static_cast<int64_t>(T - 1) * RT * 16 : R;
   const __amdgpu_buffer_rsrc_t gbuf =
-      buffer_of(a.gin + slot * R * H4, static_cast<uint32_t>(static_cast<int64_t>(R) * H4 * sizeof(float)));
+      buffer_of(a.gin + slot * gin_rows * H4, static_cast<uint32_t>(gin_rows * H4 * sizeof(float)));
 
   uint4 wh[KC], wl[KC];
   resident_weights_split<KC, true, kRad, ZW>(wh, wl, reinterpret_cast<float*>(lds), th, a.off_l, a.in_l + H, 0, H,
@@ -2318,8 +1956,13 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_stream(
         const int row = r0 + nb * 16 + lr;
         if (row < R) {
           typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[nb]), gbuf,
-                                                 static_cast<uint32_t>((row * H4 + 4 * unit) * 4), 0, 0);
+          uint32_t off = static_cast<uint32_t>((row * H4 + 4 * unit) * 4);
+          if (a.tiled) {
+            const int t = row / B, b = row - t * B;
+            off = static_cast<uint32_t>((((t * RT + (b >> 4)) * mblocks + mb) * 8 + wave) * 1024 +
+                                        ((b & 15) + 16 * lg) * 16);
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[nb]), gbuf, off, 0, 0);
         }
         acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
@@ -2385,7 +2028,6 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_dma(Fwd
   const uint2 key = stream_key(a.seeds[e], a.step);
   const uint32_t pair = static_cast<uint32_t>(a.j0 + jl), step_lo = static_cast<uint32_t>(a.step);
   const float seps = sg == 0 ? eps_of(a, e, kGroupLstm) : -eps_of(a, e, kGroupLstm);
-  const int unit = mb * 32 + wave * 4 + lg;   // output unit of this lane
   // 32-bit offsets: R 4H floats < 2^31 bytes (host check).  Every DMA offset
   // is per lane (bounds-checked): row tiles past R (B % 16 == 0) read zeros
   // and are never stored.
@@ -2451,10 +2093,11 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_dma(Fwd
 #pragma unroll
       for (int nb = 0; nb < 4; ++nb) {
         const int row = r0 + nb * 16 + lr;
-        if (row < R) {
+        if (row < R) {                        // whole tiles: R % 16 == 0
           typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[nb]), gbuf,
-                                                 static_cast<uint32_t>((row * H4 + 4 * unit) * 4), 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(
+              __builtin_bit_cast(u32x4, acc[nb]), gbuf,
+              static_cast<uint32_t>((((r0 / 16 + nb) * mblocks + mb) * 8 + wave) * 1024 + lane * 16), 0, 0);
         }
         acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
@@ -2887,7 +2530,7 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
 
 // ce of every row from the two vocabulary halves, summed per 64-row tile in
 // fp64.  Grid: (row tiles, slots of the pass); 64 threads.
-__global__ void k_ce_combine(FwdArgs a, const float2* hpart, const float* htgt) {
+static __global__ void k_ce_combine(FwdArgs a, const float2* hpart, const float* htgt) {
   __shared__ float ces[64];
   const int tile = blockIdx.x, ps = blockIdx.y;
   const int sg = ps & 1, pj = ps >> 1;
@@ -2911,7 +2554,7 @@ __global__ void k_ce_combine(FwdArgs a, const float2* hpart, const float* htgt) 
 }
 
 // Zero n words (barrier counters and the abort flag before a persistent launch).
-__global__ void k_zero_u32(unsigned* p, int n) {
+static __global__ void k_zero_u32(unsigned* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
 }

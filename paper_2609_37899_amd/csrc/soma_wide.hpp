@@ -234,8 +234,9 @@ __global__ void k_fill_f32(float* out, int64_t n) {
 // parts), as the form kernel writes it.  A is either stored split the same
 // way ([M][2][K], written so by LayerNorm and by the GELU epilogue) or fp32
 // [M][K], split as it is staged (the tied matrix of the input projection);
-// per slot, or per expert.  C is fp32 [M][N] (store, add), or split
-// [M][2][N] (GELU: the next product's A).  Block tile 128 (n) x 128 (m),
+// per slot, or per expert.  C is fp32 [M][N] (store, add), split [M][2][N]
+// (GELU: the next product's A), or the tiled gate inputs of the exchange
+// recurrence (gates: rows t B + b).  Block tile 128 (n) x 128 (m),
 // four waves of 64 x 64; K in 32-wide chunks (K % 32 == 0, N % 4 == 0)
 // staged through two LDS buffers: chunk c + 1's global loads are in flight
 // during chunk c's products and stored into the other buffer after them,
@@ -243,7 +244,7 @@ __global__ void k_fill_f32(float* out, int64_t n) {
 // the 8 XCDs round-robin) works through a contiguous range of them: the n
 // tiles of one m tile, and the m tiles of one slot, share its L2.
 // ---------------------------------------------------------------------------
-enum WideEpi { kEpiStore = 0, kEpiGelu = 1, kEpiAdd = 2 };
+enum WideEpi { kEpiStore = 0, kEpiGelu = 1, kEpiAdd = 2, kEpiGates = 3 };
 
 struct MmArgs {
   const void* A;
@@ -256,6 +257,7 @@ struct MmArgs {
   int M, N, K;
   int pcs, PC, NS;    // the pass's slots
   int ntn, ntm;       // n tiles, m tiles
+  int B;              // sequences (kEpiGates: row m is sequence m % B of step m / B)
   int64_t tiles;      // ntn * ntm * slots
   unsigned* err;
 };
@@ -376,6 +378,11 @@ __global__ __launch_bounds__(256) void k_wide_mm(MmArgs p) {
         _Float16* C = reinterpret_cast<_Float16*>(p.C) + 2 * s * p.c_slot + int64_t(m) * 2 * N + n;
         *reinterpret_cast<uint2*>(C) = hi;
         *reinterpret_cast<uint2*>(C + N) = lo;
+      } else if constexpr (kEpi == kEpiGates) {
+        const int t = m / p.B, b = m - t * p.B, RT = (p.B + 15) / 16;
+        const int64_t off = ((int64_t(t * RT + (b >> 4)) * (N / 128) + (n >> 7)) * 8 + ((n >> 4) & 7)) * 256 +
+                            ((b & 15) + 16 * ((n >> 2) & 3)) * 4;
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + s * p.c_slot + off) = v;
       } else {
         float4* c = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + s * p.c_slot + int64_t(m) * N + n);
         if constexpr (kEpi == kEpiAdd) {

@@ -33,7 +33,7 @@ CASES = {
     "h64_e64_b12": (1, 1, 64, 64, 12, 11, 2, 1e-3, 1e-2, 0, 0),  # one block per job, embedding in LDS, one row tile
     "h512_jobs": (1, 2, 32, 512, 56, 4, 12, 1e-3, 1e-3, 0, 0),   # pipelined exchange, 2 jobs in half the groups, ragged last tile
     "h256_b64_jobs": (2, 2, 32, 256, 64, 6, 20, 1e-3, 1e-2, 0, 0),  # pipelined exchange, 32 groups, uneven jobs
-    "h192_b64": (1, 2, 32, 192, 64, 7, 3, 1e-3, 1e-2, 0, 0),     # faulted the device with the pipelined exchange (skipped)
+    "h192_b64": (1, 2, 32, 192, 64, 7, 3, 1e-3, 1e-2, 0, 0),     # pipelined exchange, H / 64 odd
     "h128_b64_t3": (2, 1, 32, 128, 64, 3, 2, 1e-3, 1e-2, 0, 0),  # pipelined exchange, two steps per sequence
     "h128_b49_t2": (1, 2, 16, 128, 49, 2, 2, 1e-3, 1e-2, 0, 0),  # one step per sequence (no exchange), one row of tile 4
 }
@@ -46,16 +46,7 @@ LONG_CASES = {
     "h704_b64_t24": (1, 2, 32, 704, 64, 24, 2, 1e-3, 1e-3, 0, 0),   # 16-byte word exchange, 23 steps
 }
 
-# Cases that faulted the device and whose cause is not found: kept, skipped.
-FAULTED = {
-    "h192_b64": "the pipelined exchange recurrence at H = 192, B = 64 faulted the device (cause not found); "
-                "H = 192 now takes the staged recurrence, and this case stays off the device",
-}
-
-
 def run_case(name, distinct=True, data=None, probe=0, head_scale=1.0):
-    if name in FAULTED:
-        pytest.skip(FAULTED[name])
     torch = require_gpu()
     N, L, E, H, B, T, P, eps, lr, mode, pc = CASES[name] if name in CASES else LONG_CASES[name]
     shape = soma.Shape(N, L, E, H, B, T, P, mode, pc, probe=probe)
@@ -271,8 +262,7 @@ def test_chunking_does_not_change_the_result():
 
 
 @pytest.mark.parametrize("name,probe", [("h512_b50", 0), ("b64_h128", 1), ("h704_b64", 2), ("h512_jobs", 0),
-                                        ("h256_b64_jobs", 1), pytest.param("h192_b64", 0, marks=pytest.mark.skip(
-                                            reason=FAULTED["h192_b64"])), ("h128_b64_t3", 2), ("h128_b49_t2", 0),
+                                        ("h256_b64_jobs", 1), ("h192_b64", 0), ("h128_b64_t3", 2), ("h128_b49_t2", 0),
                                         pytest.param("h128_b10", 0, marks=pytest.mark.skip(
                                             reason="two 8-wave exchange blocks per compute unit faulted the device "
                                                    "here; that placement is disabled (cause not found)"))])
