@@ -30,9 +30,9 @@ PEAK_FP32_MFMA_TFLOPS = 157.3   # MI355X dense fp32 matrix peak
 PEAK_FP16_MFMA_TFLOPS = 2500.0  # MI355X dense fp16 matrix peak
 # Kernels whose products run on the fp16 matrix cores from split fp32
 # operands (three fp16 products per fp32 product, fp32 accumulation).
-SPLIT_F16_KERNELS = ("k_rec_xchg", "k_rec_persist", "k_rec_local", "k_rec_step_split", "k_proj_stream", "k_proj_dma",
+SPLIT_F16_KERNELS = ("k_rec_xchg", "k_rec_persist", "k_rec_local", "k_rec_step_split", "k_proj_stream", "k_mm",
                      "k_head_stream",
-                     "k_head_fused", "k_body", "k_wide_mm")
+                     "k_head_fused", "k_body")
 PEAK_HBM_GBS = 8000.0
 PROBE_LAWS = {"gaussian": 0, "sparse": 1, "dense": 2}
 
@@ -69,7 +69,7 @@ def parse():
 KERNEL_SOURCES = ("paper_2609_37899_amd/csrc/soma_kernels.hpp", "paper_2609_37899_amd/csrc/soma_xchg.hpp",
                   "paper_2609_37899_amd/csrc/soma_rng.hpp")
 BODY_SOURCES = KERNEL_SOURCES + ("paper_2609_37899_amd/csrc/soma_body.hpp",)
-WIDE_SOURCES = BODY_SOURCES + ("paper_2609_37899_amd/csrc/soma_wide.hpp",)
+WIDE_SOURCES = BODY_SOURCES + ("paper_2609_37899_amd/csrc/soma_wide.hpp", "paper_2609_37899_amd/csrc/soma_mm.hpp")
 
 
 def kernel_source_hash(kernel: str = "") -> str:
@@ -78,7 +78,7 @@ def kernel_source_hash(kernel: str = "") -> str:
     from paper_2609_37899_amd.build import HIPCC_FLAGS
     h = hashlib.sha256()
     h.update(" ".join(HIPCC_FLAGS).encode())
-    srcs = BODY_SOURCES if kernel == "k_body" else (WIDE_SOURCES if kernel.startswith("k_wide") else KERNEL_SOURCES)
+    srcs = BODY_SOURCES if kernel == "k_body" else (WIDE_SOURCES if kernel.startswith("k_wide") or kernel == "k_mm" else KERNEL_SOURCES)
     for f in srcs:
         h.update(open(os.path.join(ROOT, f), "rb").read())
     return h.hexdigest()[:16]
@@ -290,22 +290,21 @@ def main():
     traffic = None
     # The kernels the library picks for this shape (see soma_api.hip):
     # streaming projection and head where H % 64 == 0, H <= 704 and one
-    # slot's gate inputs stay under 2^31 bytes (the projection from the
-    # pre-split sequence after the exchange recurrence in fragment order with
-    # B = 64); the recurrence one block per job at H = 64, else persistent (one
+    # slot's gate inputs stay under 2^31 bytes (the projection as a batched
+    # product of the sequence that the exchange recurrence stores split); the
+    # recurrence one block per job at H = 64, else persistent (one
     # launch per layer and chunk) unless it ran per time step (split fp16
     # products where H % 32 == 0).
     streams = (w.hidden % 64 == 0 and w.hidden <= 704
                and (w.seq_len - 1) * w.batch * 4 * w.hidden * 4 < 2 ** 31)
-    presplit = (streams and phases.get("xchg_launches", 0) > 0 and w.batch == 64
-                and w.hidden in (128, 256, 512))
+    presplit = streams and phases.get("xchg_launches", 0) > 0
     kname = {"rec": "k_rec_step_split" if w.hidden % 32 == 0 else "k_rec_step",
-             "proj": ("k_proj_dma" if presplit else "k_proj_stream") if streams else "k_proj", "fold": "k_fold",
+             "proj": ("k_mm" if presplit else "k_proj_stream") if streams else "k_proj", "fold": "k_fold",
              "head": ("k_head_fused" if w.hidden <= 128 else "k_head_stream") if streams else "k_head_ce"}[dom]
     if w.arch == 1:
         kname = "k_body"          # the whole perturbed forward, one launch per direction chunk
     elif w.arch == 2:
-        kname = {"rec": "k_rec_persist", "proj": "k_wide_mm", "fold": "k_wide_form", "head": "k_wide_head"}[dom]
+        kname = {"rec": "k_rec_xchg" if phases.get("xchg_launches", 0) > 0 else "k_rec_persist", "proj": "k_mm", "fold": "k_wide_form", "head": "k_wide_head"}[dom]
     elif dom == "rec" and launches["rec"] < w.n_layers * (w.seq_len - 1):
         kname = ("k_rec_local" if local_rec else
                  "k_rec_xchg" if phases.get("xchg_launches", 0) > 0 else "k_rec_persist")

@@ -125,8 +125,8 @@ enum soma_flags {
   /* Store each layer's output sequence in fp32 and let the next layer's
    * streaming projection split it while staging it, even where the
    * exchange recurrence stores it pre-split in fragment order for the
-   * DMA-staged projection (B = 64, H = 128, 256, 512).  Both split the same
-   * fp32 values the same way, so results agree bit for bit. */
+   * batched product (B > 32).  Both split the same fp32 values the same way
+   * and sum them in the same order, so results agree bit for bit. */
   SOMA_FLAG_FP32_SEQUENCE = 8
 };
 
@@ -462,9 +462,9 @@ int soma_estimator_moments(soma_ctx* ctx, const uint64_t* seeds_dev, uint64_t st
 typedef struct soma_phase_times {
   float fold_ms;          /* layer-1 gate inputs per byte value (k_fold; 0 where
                              the H = 64 recurrence forms them in the block) */
-  float proj_ms;          /* input projections of layers >= 2 (k_proj_dma from a
-                             pre-split sequence, k_proj_stream, or the tiled
-                             k_proj) */
+  float proj_ms;          /* input projections of layers >= 2 (k_form_gates and
+                             k_mm from a pre-split sequence, k_proj_stream, or the
+                             tiled k_proj) */
   float rec_ms;           /* recurrent time steps of all layers (k_rec_xchg or
                              k_rec_persist or, at H = 64, k_rec_local: one launch per layer and
                              chunk; or k_rec_step, one per time step); for

@@ -5,10 +5,9 @@
 //   k_fold          layer-1 gate inputs per byte value (embedding times the
 //                   input weights, perturbed rows formed on the fly)
 //   per layer l:    for l >= 2, h^(l-1) times the input weights, weights
-//                   held in registers: k_proj_dma where the previous layer's
-//                   k_rec_xchg stored its h pre-split (B % 16 = 0,
-//                   H = 128, 256, 512), else k_proj_stream; then the
-//                   recurrence:
+//                   k_form_gates + k_mm where the previous layer's k_rec_xchg
+//                   stored its h pre-split, else k_proj_stream (weights held
+//                   in registers); then the recurrence:
 //                   k_rec_xchg (B > 32: one cooperative launch, row tiles of
 //                   the batch pipelined, h exchanged pre-split by LDS DMA)
 //                   or k_rec_persist (one cooperative launch; blocks of a
@@ -25,7 +24,7 @@
 // The paper's width-32 body (SOMA_ARCH_BODY) runs its whole perturbed
 // forward in k_body (soma_body.hpp); the wide controls' body
 // (SOMA_ARCH_WIDE) forms each slot's perturbed weights once (k_wide_form)
-// and runs split-fp16 products (k_wide_mm), LayerNorms and the decoder
+// and runs split-fp16 products (k_mm), LayerNorms and the decoder
 // (soma_wide.hpp) around k_rec_xchg or k_rec_persist on the pre-formed weights.  Every kernel that forms split fp16
 // weights checks their range and the persistent recurrence bounds its waits:
 // either failure sets a sticky flag, and the step is then aborted on the
@@ -46,6 +45,7 @@
 #include "soma.h"
 #include "soma_kernels.hpp"
 #include "soma_body.hpp"
+#include "soma_mm.hpp"
 #include "soma_wide.hpp"
 #include "soma_rec.hpp"
 
@@ -94,7 +94,10 @@ struct Layout {
   // SOMA_ARCH_WIDE: pre-formed weights and the residual stream per slot
   // (hseq holds the normalised rows and the recurrence's h, gin the gate
   // inputs and the MLP hidden layer)
-  size_t wform = 0, xres = 0;
+  size_t wform = 0, xres = 0, esplit = 0;
+  // Stacked LSTM on the exchange recurrence with more than one layer: a
+  // layer's perturbed input weights per slot (0: k_proj_stream keeps its own)
+  size_t wproj = 0, wproj_bytes = 0;
 };
 
 // Directions per update: n_pairs per accumulation batch, accum batches.
@@ -210,7 +213,7 @@ Layout layout_for_wide(const soma_config& c, int pc) {
   L.delta_chunks = int((R + soma::kDeltaChunk - 1) / soma::kDeltaChunk);
   const size_t slots = std::max(N * size_t(pc) * 2, N);
   const size_t form = size_t(soma::wide_form_layout(int(dp), c.n_layers).total);
-  const size_t E = soma::kWideHeadWidth;
+  const size_t E = soma::kWideHeadWidth, R16 = (R + 15) / 16 * 16;   // whole row tiles
   size_t at = 0;
   L.sync = at; at += round_up(sizeof(unsigned) * (kMaxGroups + 1));
   L.rates = at; at += round_up(sizeof(float) * 2 * N);
@@ -220,8 +223,9 @@ Layout layout_for_wide(const soma_config& c, int pc) {
   L.wform = at; at += round_up(sizeof(float) * slots * form);
   L.U = at; at += round_up(sizeof(float) * slots * SOMA_VOCAB * dp);
   L.xres = at; at += round_up(sizeof(float) * slots * R * dp);
-  L.hseq = at; at += round_up(sizeof(float) * slots * R * dp);
-  L.gin = at; at += round_up(sizeof(float) * slots * gin_rows(c) * 4 * dp);
+  L.hseq = at; at += round_up(sizeof(float) * slots * R16 * dp);
+  L.gin = at; at += round_up(sizeof(float) * slots * std::max(size_t(gin_rows(c)), R16) * 4 * dp);
+  L.esplit = at; at += round_up(sizeof(float) * N * SOMA_VOCAB * E);
   L.fdec = at; at += round_up(sizeof(float) * N * R * E);
   L.lse = at; at += round_up(sizeof(float) * N * R);
   L.dpart = at; at += round_up(sizeof(float) * N * L.delta_chunks * SOMA_VOCAB * E);
@@ -283,7 +287,16 @@ void add_xchg(const soma_config& c, Layout* L, size_t* at) {
   *at += round_up(L->xch_bytes + sizeof(unsigned) * xchg_counter_words());
 }
 
-Layout layout_for(const soma_config& c, int pc) {
+// Whether a layer's projection runs as a batched product on the sequence that
+// the exchange recurrence stores split.
+bool mm_projection(const soma_config& c) {
+  return c.arch == SOMA_ARCH_LSTM && c.n_layers > 1 && xchg_shape(c) && stream_weights(c) &&
+         !(c.flags & SOMA_FLAG_FP32_SEQUENCE);
+}
+
+// `preformed` = false leaves out the area of a layer's pre-formed input weights
+// (the projection then keeps them in registers: the same sums).
+Layout layout_for(const soma_config& c, int pc, bool preformed = true) {
   if (c.arch == SOMA_ARCH_BODY) return layout_for_body(c, pc);
   if (c.arch == SOMA_ARCH_WIDE) return layout_for_wide(c, pc);
   Layout L;
@@ -308,7 +321,8 @@ Layout layout_for(const soma_config& c, int pc) {
   // of an evaluation where the H = 64 recurrence forms them in the block.
   const size_t uslots = local_embedding(c) ? N : slots;
   L.U = at;    at += round_up(sizeof(float) * uslots * SOMA_VOCAB * 4 * H);
-  L.hseq = at; at += round_up(sizeof(float) * slots * R * H);
+  const bool mm = preformed && mm_projection(c);
+  L.hseq = at; at += round_up(sizeof(float) * slots * (mm ? size_t(tile_rows(c)) : R) * H);
   L.cst = at;  at += round_up(sizeof(float) * slots * B * H);
   // Head partials of k_head_stream only (H > 128; k_head_fused keeps its own).
   const size_t hslots = stream_weights(c) && H > 128 ? slots : 0;
@@ -316,6 +330,11 @@ Layout layout_for(const soma_config& c, int pc) {
   L.htgt = at; at += round_up(sizeof(float) * hslots * R);
   L.gin = at;
   if (c.n_layers > 1) at += round_up(sizeof(float) * slots * gin_rows(c) * 4 * H);
+  if (mm) {
+    L.wproj = at;
+    L.wproj_bytes = sizeof(float) * slots * 4 * H * H;
+    at += round_up(L.wproj_bytes);
+  }
   add_xchg(c, &L, &at);
   L.total = at;
   return L;
@@ -351,6 +370,7 @@ struct soma_ctx {
   unsigned spin_limit;              // polls per group barrier of the persistent recurrence
   bool have_times;
   // device facts for the persistent recurrence
+  int cus;                          // compute units of the device
   int coop_blocks;                  // co-resident k_rec_persist blocks (0: path unavailable)
   int xchg_per_cu;                  // co-resident k_rec_xchg blocks per compute unit (0: unavailable)
   int xchg_cus_per_xcd;
@@ -928,28 +948,6 @@ void launch_proj_stream(const soma::FwdArgs& a, int nslots, hipStream_t st) {
     launch_proj_stream_t<true>(a, nslots, st);
 }
 
-// The projection from a pre-split sequence (k_proj_dma), for the widths at
-// which the exchange recurrence stores it (fragment order: H = 128, 256, 512).
-bool proj_dma_width(int H) { return H == 128 || H == 256 || H == 512; }
-
-template <bool kRad>
-void launch_proj_dma_t(const soma::FwdArgs& a, int nslots, hipStream_t st) {
-  const int mblocks = a.H / 32;
-  const dim3 grid(unsigned(nslots * mblocks)), block(soma::kProjThreads);
-  switch (a.H / 64) {
-    case 2: hipLaunchKernelGGL((soma::k_proj_dma<2, kRad>), grid, block, 0, st, a, mblocks, nslots); break;
-    case 4: hipLaunchKernelGGL((soma::k_proj_dma<4, kRad>), grid, block, 0, st, a, mblocks, nslots); break;
-    default: hipLaunchKernelGGL((soma::k_proj_dma<8, kRad>), grid, block, 0, st, a, mblocks, nslots); break;
-  }
-}
-
-void launch_proj_dma(const soma::FwdArgs& a, int nslots, hipStream_t st) {
-  if (a.probe == SOMA_PROBE_GAUSSIAN)
-    launch_proj_dma_t<false>(a, nslots, st);
-  else
-    launch_proj_dma_t<true>(a, nslots, st);
-}
-
 // H = 64 (and the persistent path's other conditions: B <= 64, one slot's
 // gate inputs under 2^31 bytes): the recurrence runs one block per job with
 // h kept in LDS between steps (k_rec_local).
@@ -1044,6 +1042,69 @@ int launch_xchg(soma_ctx* ctx, const soma::FwdArgs& a, int xgroups, int slots, b
   return SOMA_OK;
 }
 
+// k_mm with TN x TM row tiles per block and WN x WM waves.
+template <int kEpi, int TN, int TM, int WN, int WM>
+int launch_mm_t(soma::MmArgs m, int slots, int cus, hipStream_t st) {
+  m.ntn = (m.N + 16 * TN - 1) / (16 * TN);
+  m.ntm = (m.M + 16 * TM - 1) / (16 * TM);
+  m.tiles = int64_t(m.ntn) * m.ntm * slots;
+  int64_t blocks = (m.tiles + soma::kXcds - 1) / soma::kXcds * soma::kXcds;
+  if (WN * WM == 8) blocks = std::min(blocks, int64_t(std::max(cus / soma::kXcds, 1)) * soma::kXcds);
+  if (blocks >= (int64_t(1) << 31)) return fail(SOMA_ESHAPE, "too many product tiles in one launch");
+  constexpr unsigned lds = soma::mm_lds_bytes(TN, TM);
+  const void* kern = reinterpret_cast<const void*>(&soma::k_mm<kEpi, TN, TM, WN, WM>);
+  if (lds > 65536u) {
+    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return fail(SOMA_EDEVICE, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+  }
+  hipLaunchKernelGGL((soma::k_mm<kEpi, TN, TM, WN, WM>), dim3(static_cast<unsigned>(blocks)), dim3(64 * WN * WM), lds,
+                     st, m);
+  return check_launch("k_mm");
+}
+
+// One batched product (soma_mm.hpp) over `slots` slots.  Large tiles where N
+// fills them: 256 x 256, or 384 x 128 where N is a multiple of 384 only (the
+// down projection at d_p = 384); 128 x 128 else.  At the wide control's sizes
+// (64 slots, 65,472 rows, K = 384) against 128 x 128 throughout: gates (N =
+// 1,536) 13.0 against 16.0 ms, GELU 15.1 against 16.8, down projection (N = 384,
+// K = 1,536) 13.5 against 14.6.
+template <int kEpi>
+int launch_mm(soma::MmArgs m, int slots, int cus, hipStream_t st) {
+  if (m.N % 256 == 0) return launch_mm_t<kEpi, 16, 16, 2, 4>(m, slots, cus, st);
+  if (m.N % 384 == 0) return launch_mm_t<kEpi, 24, 8, 4, 2>(m, slots, cus, st);
+  return launch_mm_t<kEpi, 8, 8, 2, 2>(m, slots, cus, st);
+}
+
+// The input projection of layer a.layer >= 1 from the sequence that the
+// exchange recurrence stored split: perturbed weights, then one product per
+// slot into the tiled gate inputs.
+int launch_mm_projection(const soma_ctx* ctx, const soma::FwdArgs& a, hipStream_t st) {
+  const soma_config& c = ctx->cfg;
+  const int64_t H = c.hidden, rows = tile_rows(c);
+  _Float16* w = reinterpret_cast<_Float16*>(ctx->ws + ctx->lay.wproj);
+  const dim3 grid(unsigned(4 * H / 16 * (H / 32) / 4), unsigned(a.N * a.pcs));
+  if (a.probe == SOMA_PROBE_GAUSSIAN)
+    hipLaunchKernelGGL((soma::k_form_gates<false>), grid, dim3(256), 0, st, a, w);
+  else
+    hipLaunchKernelGGL((soma::k_form_gates<true>), grid, dim3(256), 0, st, a, w);
+  if (int rc = check_launch("k_form_gates")) return rc;
+  soma::MmArgs m{};
+  m.A = reinterpret_cast<const _Float16*>(a.hseq);
+  m.a_slot = rows * H;
+  m.W = w;
+  m.w_slot = 4 * H * H;
+  m.C = a.gin;
+  m.c_slot = rows * 4 * H;
+  m.M = int(rows);
+  m.N = int(4 * H);
+  m.K = int(H);
+  m.pcs = a.pcs;
+  m.PC = a.PC;
+  m.NS = 2;
+  m.err = a.err;
+  return launch_mm<soma::kEpiGates>(m, 2 * a.N * a.pcs, ctx->cus, st);
+}
+
 // The paper's body: one fused launch per pass (SOMA_ARCH_BODY).
 template <int DW, int D, bool kPert>
 void launch_body_t(const soma::BodyArgs& a, unsigned blocks, hipStream_t st) {
@@ -1093,27 +1154,6 @@ int run_body(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
 // The wide controls' body: one pass of the kernels listed in soma_wide.hpp
 // over the pass's slots (expert, direction, sign), or over the experts
 // unperturbed (!kPert).
-// epi: soma::WideEpi; a_split: A stored split (else fp32, split as staged).
-int launch_wide_mm(int epi, bool a_split, soma::MmArgs m, int slots, hipStream_t st) {
-  m.ntn = (m.N + 127) / 128;
-  m.ntm = (m.M + 127) / 128;
-  m.tiles = int64_t(m.ntn) * m.ntm * slots;
-  const int64_t blocks = (m.tiles + soma::kXcds - 1) / soma::kXcds * soma::kXcds;
-  if (blocks >= (int64_t(1) << 31)) return fail(SOMA_ESHAPE, "too many product tiles in one launch");
-  const dim3 grid(static_cast<unsigned>(blocks)), block(256);
-  if (!a_split)
-    hipLaunchKernelGGL((soma::k_wide_mm<false, soma::kEpiStore>), grid, block, 0, st, m);
-  else if (epi == soma::kEpiGelu)
-    hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiGelu>), grid, block, 0, st, m);
-  else if (epi == soma::kEpiAdd)
-    hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiAdd>), grid, block, 0, st, m);
-  else if (epi == soma::kEpiGates)
-    hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiGates>), grid, block, 0, st, m);
-  else
-    hipLaunchKernelGGL((soma::k_wide_mm<true, soma::kEpiStore>), grid, block, 0, st, m);
-  return check_launch("k_wide_mm");
-}
-
 template <bool kPert>
 int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t step, const float* eps_v,
              int eps_stride, const uint8_t* bytes, int j0, int pcs, hipStream_t st) {
@@ -1122,7 +1162,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   const int N = c.n_experts, D = c.n_layers, dt = c.hidden, dp = soma::wide_padded(dt);
   const int NS = kPert ? 2 : 1, PC = kPert ? L.pc : 1;
   const int slots = N * pcs * NS;
-  const int64_t R = int64_t(c.seq_len - 1) * c.batch;
+  const int64_t R = int64_t(c.seq_len - 1) * c.batch, R16 = (R + 15) / 16 * 16;
   const soma::WideForm F = soma::wide_form_layout(dp, D);
   const int64_t mp = 4 * int64_t(dp) * dp;
   unsigned* err = reinterpret_cast<unsigned*>(ctx->ws + L.sync) + kMaxGroups;
@@ -1171,10 +1211,15 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     hipLaunchKernelGGL(soma::k_fill_f32, dim3(4096), dim3(256), 0, st, a.wform, form_floats);
     if (int rc = check_launch("k_fill_f32")) return rc;
   }
-  const int64_t mat_quads = (L.d - (2LL * D + 1) * dt) / 4;
-  hipLaunchKernelGGL((soma::k_wide_form<kPert>), dim3(unsigned((mat_quads + 255) / 256), unsigned(slots)), dim3(256),
-                     0, st, a);
+  hipLaunchKernelGGL((soma::k_wide_form<kPert>),
+                     dim3(unsigned((dt + soma::kFormThreads - 1) / soma::kFormThreads),
+                          unsigned(soma::wide_form_rows(dt, D)), unsigned(slots)),
+                     dim3(soma::kFormThreads), 0, st, a);
   if (int rc = check_launch("k_wide_form")) return rc;
+  float* esplit = reinterpret_cast<float*>(ctx->ws + L.esplit);
+  hipLaunchKernelGGL(soma::k_wide_split, dim3(SOMA_VOCAB * 4 / 256, unsigned(N)), dim3(256), 0, st, ctx->head,
+                     ctx->head_stride, esplit, err);
+  if (int rc = check_launch("k_wide_split")) return rc;
   if (int rc = mark(ctx, kPhaseFold, st)) return rc;
 
   soma::MmArgs m{};
@@ -1183,19 +1228,19 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   m.NS = NS;
   m.err = err;
   m.w_slot = F.total;
-  m.B = c.batch;
+  m.B = c.batch % 16 == 0 ? 0 : c.batch;
   // U = E P_in^T: the input projection of every byte value.
-  m.A = ctx->head;
-  m.a_slot = ctx->head_stride;
+  m.A = reinterpret_cast<const _Float16*>(esplit);
+  m.a_slot = int64_t(SOMA_VOCAB) * soma::kWideHeadWidth;
   m.a_expert = 1;
-  m.W = a.wform + F.pin;
+  m.W = reinterpret_cast<const _Float16*>(a.wform + F.pin);
   m.C = a.U;
   m.c_slot = int64_t(SOMA_VOCAB) * dp;
   m.M = SOMA_VOCAB;
   m.N = dp;
   m.K = soma::kWideHeadWidth;
-  if (int rc = launch_wide_mm(soma::kEpiStore, false, m, slots, st)) return rc;
-  const dim3 ln_grid(unsigned((R + 3) / 4), unsigned(slots));
+  if (int rc = launch_mm<soma::kEpiStore>(m, slots, ctx->cus, st)) return rc;
+  const dim3 ln_grid(unsigned((R + 15) / 16), unsigned(slots));
   hipLaunchKernelGGL((soma::k_wide_ln<0>), ln_grid, dim3(256), 0, st, a);
   if (int rc = check_launch("k_wide_ln")) return rc;
   if (int rc = mark(ctx, kPhaseFold, st)) return rc;
@@ -1205,14 +1250,16 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   for (int l = 0; l < D; ++l) {
     const float* blk = a.wform + F.blk0 + l * F.blk_stride;
     // gate inputs gin = n A'^T (rows interleaved per unit)
-    m.A = a.n;
-    m.a_slot = R * dp;
-    m.W = blk;
+    m.A = reinterpret_cast<const _Float16*>(a.n);
+    m.a_slot = R16 * dp;
+    m.W = reinterpret_cast<const _Float16*>(blk);
     m.C = a.gin;
     m.c_slot = (xgroups > 0 ? tile_rows(c) : R) * 4 * dp;
     m.N = 4 * dp;
     m.K = dp;
-    if (int rc = launch_wide_mm(xgroups > 0 ? soma::kEpiGates : soma::kEpiStore, true, m, slots, st)) return rc;
+    if (int rc = xgroups > 0 ? launch_mm<soma::kEpiGates>(m, slots, ctx->cus, st)
+                             : launch_mm<soma::kEpiStore>(m, slots, ctx->cus, st))
+      return rc;
     if (int rc = mark(ctx, kPhaseProj, st)) return rc;
     ++ctx->proj_launches;
     // the recurrence on the pre-formed R; h into the n buffer
@@ -1222,6 +1269,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     f.seeds = seeds;
     f.gin = a.gin;
     f.hseq = a.n;
+    f.hrows = R16;
     f.d = L.d;
     f.step = step;
     f.eps_v = eps_v;
@@ -1266,22 +1314,22 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     // x += h; n = LN(x); m = GELU(n U'^T); x += m V^T
     hipLaunchKernelGGL((soma::k_wide_ln<1>), ln_grid, dim3(256), 0, st, a);
     if (int rc = check_launch("k_wide_ln")) return rc;
-    m.A = a.n;
-    m.a_slot = R * dp;
-    m.W = blk + 2 * mp;
+    m.A = reinterpret_cast<const _Float16*>(a.n);
+    m.a_slot = R16 * dp;
+    m.W = reinterpret_cast<const _Float16*>(blk + 2 * mp);
     m.C = a.gin;
-    m.c_slot = R * 4 * dp;
+    m.c_slot = R16 * 4 * dp;
     m.N = 4 * dp;
     m.K = dp;
-    if (int rc = launch_wide_mm(soma::kEpiGelu, true, m, slots, st)) return rc;
-    m.A = a.gin;
-    m.a_slot = R * 4 * dp;
-    m.W = blk + 3 * mp;
+    if (int rc = launch_mm<soma::kEpiGelu>(m, slots, ctx->cus, st)) return rc;
+    m.A = reinterpret_cast<const _Float16*>(a.gin);
+    m.a_slot = R16 * 4 * dp;
+    m.W = reinterpret_cast<const _Float16*>(blk + 3 * mp);
     m.C = a.x;
     m.c_slot = R * dp;
     m.N = dp;
     m.K = 4 * dp;
-    if (int rc = launch_wide_mm(soma::kEpiAdd, true, m, slots, st)) return rc;
+    if (int rc = launch_mm<soma::kEpiAdd>(m, slots, ctx->cus, st)) return rc;
     if (l + 1 < D) {
       hipLaunchKernelGGL((soma::k_wide_ln<2>), ln_grid, dim3(256), 0, st, a);
       if (int rc = check_launch("k_wide_ln")) return rc;
@@ -1292,14 +1340,14 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   hipLaunchKernelGGL((soma::k_wide_ln<2>), ln_grid, dim3(256), 0, st, a);
   if (int rc = check_launch("k_wide_ln")) return rc;
   // u = n P_out'^T into the (free) gate-input buffer, then the decoder.
-  m.A = a.n;
-  m.a_slot = R * dp;
-  m.W = a.wform + F.pout;
+  m.A = reinterpret_cast<const _Float16*>(a.n);
+  m.a_slot = R16 * dp;
+  m.W = reinterpret_cast<const _Float16*>(a.wform + F.pout);
   m.C = a.gin;
   m.c_slot = R * 4 * dp;
   m.N = soma::kWideHeadWidth;
   m.K = dp;
-  if (int rc = launch_wide_mm(soma::kEpiStore, true, m, slots, st)) return rc;
+  if (int rc = launch_mm<soma::kEpiStore>(m, slots, ctx->cus, st)) return rc;
   hipLaunchKernelGGL((soma::k_wide_head<!kPert>), dim3(unsigned(L.row_tiles), unsigned(slots)), dim3(256), 0, st, a,
                      a.gin, R * 4 * dp, soma::kWideHeadWidth);
   if (int rc = check_launch("k_wide_head")) return rc;
@@ -1346,6 +1394,7 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
   const int H = c.hidden, N = c.n_experts;
   const int64_t R = int64_t(c.seq_len - 1) * c.batch;
 
+  a.hrows = R;
   a.layer = 0;
   a.in_l = c.embed;
   a.off_l = L.off_layer[0];
@@ -1371,8 +1420,7 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
     a.off_l = L.off_layer[l];
     if (l > 0) {
       if (split_h) {
-        launch_proj_dma(a, 2 * N * pcs, st);
-        if (int rc = check_launch("k_proj_dma")) return rc;
+        if (int rc = launch_mm_projection(ctx, a, st)) return rc;
       } else if (kPert && stream_weights(c)) {
         launch_proj_stream(a, 2 * N * pcs, st);
         if (int rc = check_launch("k_proj_stream")) return rc;
@@ -1394,9 +1442,9 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       if (int rc = launch_local(a, jobs, c.batch, c.probe, kx, fused_head, st)) return rc;
       ctx->rec_launches += 1;
     } else if (xgroups > 0) {
-      // The next layer's projection reads this layer's h pre-split (k_proj_dma).
-      out_split = l + 1 < c.n_layers && stream_weights(c) && proj_dma_width(H) && c.batch % 16 == 0 &&
-                  !(c.flags & SOMA_FLAG_FP32_SEQUENCE);
+      // The next layer's projection reads this layer's h pre-split (k_mm).
+      out_split = l + 1 < c.n_layers && L.wproj_bytes > 0;
+      a.hrows = out_split ? tile_rows(c) : R;
       if (int rc = launch_xchg(ctx, a, xgroups, 2 * N * pcs, l == 0, out_split, st)) return rc;
     } else if (groups > 0) {
       soma::PersistArgs p{};
@@ -1460,6 +1508,13 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
   ctx->ws_bytes = ws_bytes;
   ctx->have_coef = false;
   ctx->coop_blocks = 0;
+  ctx->cus = 0;
+  {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      ctx->cus = 256;
+  }
   {
     // Co-resident blocks for the persistent recurrence on the current device.
     int dev = 0, coop = 0, cus = 0, per_cu = 0, lds_max = 0;
@@ -2126,7 +2181,7 @@ int scratch_address(char** out) {
 // to what they need on the staged recurrence; the exchange's area lies beyond
 // it, except for the batches and widths that have always counted it.
 size_t scratch_need(const soma_config& c, int pc) {
-  const Layout L = layout_for(c, pc);
+  const Layout L = layout_for(c, pc, false);
   const int H = c.hidden;
   if (L.xch_bytes == 0) return L.total;
   const bool counted = c.batch > 48 && c.batch <= 64 && (H == 128 || H == 256 || H == 512 || H == 704);
@@ -2154,7 +2209,7 @@ extern "C" int soma_spsa_step_noalloc(const soma_config* cfg, float* theta, cons
                 scratch_need(*cfg, 1), kStaticScratchBytes);
   char* ws = nullptr;
   if (int rc = scratch_address(&ws)) return rc;
-  const Layout L = layout_for(*cfg, pc);
+  const Layout L = layout_for(*cfg, pc, false);
   soma_ctx ctx;   // host stack: its event pool stays empty (no phase timing here)
   init_ctx(&ctx, *cfg, L, ws, kStaticScratchBytes + kExchangeScratchBytes);
   return soma_spsa_step(&ctx, theta, seeds, step, eps, lr, bytes, losses, stream);

@@ -250,6 +250,7 @@ struct FwdArgs {
   int N, E, H, B, T, PC;  // PC = slot stride in directions
   int pcs;                // directions in this pass (grid extent)
   int j0;                 // first direction of the chunk
+  int64_t hrows;          // rows of hseq from one slot to the next (the persistent recurrences)
   int tiled;              // U and gin in the tiled order of the exchange recurrence
   int layer;              // current layer (0-based)
   int in_l;               // input width of the current layer
@@ -257,10 +258,9 @@ struct FwdArgs {
   int row_tiles;          // head row tiles per slot
   // The persistent recurrence's pre-formed instantiation only: perturbed
   // recurrent weights formed beforehand, slot s's matrix at wpre + s *
-  // wpre_slot, [4H][2][H] halves (each row's hi parts, then its lo parts)
-  // with row 4 u + g = gate g of unit u; and the signs
-  // per direction of the pass (1: one unperturbed job per expert, else both
-  // signs).
+  // wpre_slot, [4H][H] in fragment order (soma_mm.hpp) with row 4 u + g = gate
+  // g of unit u; and the signs per direction of the pass (1: one unperturbed
+  // job per expert, else both signs).
   const float* wpre;
   int64_t wpre_slot;
   int ns;
@@ -898,6 +898,14 @@ __device__ __forceinline__ void wait_vmem() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): every memory access of this wave has completed
 }
 
+// Waits until at most N of this wave's memory accesses are outstanding (they
+// complete in order, loads, stores and LDS DMA alike).
+template <int N>
+__device__ __forceinline__ void wait_vmem_but() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+
 __device__ __forceinline__ void group_arrive(unsigned* bar) {
   wait_vmem();
   __syncthreads();
@@ -1085,7 +1093,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_rec_persist(PersistArgs p) {
     const uint32_t pair = static_cast<uint32_t>(a.j0 + jl), step_lo = static_cast<uint32_t>(a.step);
     const int64_t slot = (static_cast<int64_t>(e) * a.PC + jl) * (one_sign ? 1 : 2) + sg;
     const float seps = kPre ? 0.0f : (sg == 0 ? eps_of(a, e, kGroupLstm) : -eps_of(a, e, kGroupLstm));
-    const __amdgpu_buffer_rsrc_t hbuf = buffer_of(a.hseq + slot * R * H, slot_bytes);
+    const __amdgpu_buffer_rsrc_t hbuf = buffer_of(a.hseq + slot * (kPre ? a.hrows : R) * H, slot_bytes);
     // Gate inputs of layer 1 (folded, per byte value) or of a later layer.
     const __amdgpu_buffer_rsrc_t gbuf =
         a.layer == 0 ? buffer_of(a.U + slot * kVocab * H4, static_cast<uint32_t>(kVocab * H4 * sizeof(float)))
@@ -1097,15 +1105,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_rec_persist(PersistArgs p) {
     // and held as split fragments.
     uint4 wh[KC], wl[KC];
     if constexpr (kPre) {
-      // Rows of the pre-formed matrix, stored split (a row's H hi parts,
-      // then its H lo parts): this lane's gate row, 8 consecutive k per
-      // 32-wide chunk (the range was checked where the weights were formed).
+      // Fragments as the pre-formed matrix stores them (the range was checked
+      // where they were formed).
       const _Float16* wr = reinterpret_cast<const _Float16*>(a.wpre + slot * a.wpre_slot) +
-                           static_cast<int64_t>(utile * 16 * NW + wave * 16 + lr) * 2 * H + 8 * lg;
+                           static_cast<int64_t>(utile * NW + wave) * 2 * KC * 512 + lane * 8;
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
-        wh[c] = *reinterpret_cast<const uint4*>(wr + 32 * c);
-        wl[c] = *reinterpret_cast<const uint4*>(wr + H + 32 * c);
+        wh[c] = *reinterpret_cast<const uint4*>(wr + c * 512);
+        wl[c] = *reinterpret_cast<const uint4*>(wr + (KC + c) * 512);
       }
     } else {
       resident_weights_split<KC, true, kRad, ZW, 16 * NW>(wh, wl, reinterpret_cast<float*>(lds), th, a.off_l, in + H,
@@ -1292,7 +1299,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_rec_persist(PersistArgs p) {
 }
 
 // The exchange recurrence (soma_xchg.hpp): constants and arguments, and the
-// LDS DMA it shares with the projection.
+// LDS DMA it shares with the batched products (soma_mm.hpp).
 constexpr int kXchgMaxGroups = 256;    // groups of one launch (flags in the workspace)
 constexpr int kXchgFlagWords = 256;    // flag words per group: [tile][block], H / 32 <= 64 blocks
 constexpr int kXchgCuSlots = 8 * 64;   // blocks-per-compute-unit counters: (XCD, shader engine, CU)
@@ -1314,7 +1321,7 @@ struct XchgArgs {
   int jobs;              // slots of this pass (N * directions * signs) * bblocks
   int bblocks;           // 64-sequence blocks of the batch
   unsigned spin_limit;   // polls per wait before giving up
-  int split_out;         // store the layer's h to hseq split, in fragment-order blocks (for k_proj_dma)
+  int split_out;         // store the layer's h to hseq in fragment order, whole row tiles per step (for k_mm)
 };
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -1969,139 +1976,6 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_stream(
     }
     if (c + 1 < nchunks) sstore(buf ^ 1);
     __syncthreads();
-  }
-}
-
-// ---------------------------------------------------------------------------
-// The input projection of k_proj_stream from a pre-split sequence
-// (k_proj_dma): where the previous layer's recurrence stored its h already
-// split into fp16 parts, in MFMA fragment order -- hseq as 1 KiB blocks
-// [16-row tile][hi, lo][32-wide k chunk], word 16 lg + lr holding row lr,
-// k 8 lg .. + 7 (the same bytes as fp32) -- the ring is filled by LDS DMA
-// (buffer_load_dwordx4 ... lds), one contiguous block per instruction, and
-// the products read each fragment as one 16-byte word.  Staging
-// then takes no registers, vector instructions, LDS stores or waits beside
-// the products: the DMA of the next ring chunk is issued before the current
-// chunk's products, and one wait and one barrier close each chunk.  The
-// split is the one k_proj_stream applies while staging, so the products and
-// results are the same.  The gate inputs of a finished 64-row tile are
-// stored after the barrier, so the next wait finds them done.
-// ---------------------------------------------------------------------------
-template <int NCH, bool kRad>
-__global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_dma(FwdArgs a, int mblocks, int nslots) {
-  constexpr int KC = 2 * NCH;                 // 32-wide k chunks: K = H = 64 NCH
-  constexpr int NQ = NCH % 4 == 0 ? NCH / 4 : (NCH > 8 ? (NCH % 2 == 0 ? NCH / 2 : NCH) : split_quarters(NCH));
-  constexpr int QC = KC / NQ;                 // k chunks per ring chunk
-  constexpr int KW = QC * 32;                 // k per ring chunk
-  constexpr int FRAG = 512;                   // halves per 1 KiB block
-  constexpr int NBLK = 2 * 4 * QC;            // blocks per ring chunk: (part, row tile, k chunk)
-  constexpr int BUF = NBLK * FRAG;            // halves per ring buffer
-  constexpr int BPW = (NBLK + 7) / 8;         // blocks per wave
-  constexpr int RING_BYTES = 2 * BUF * 2;
-  constexpr int ZW = KC * 32 < kZpiece ? KC * 32 : kZpiece;   // probe piece width
-  constexpr int ZS_BYTES = 128 * (ZW + 8) * 4;
-  constexpr int LDS_BYTES = RING_BYTES > ZS_BYTES ? RING_BYTES : ZS_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char lds[LDS_BYTES];
-  _Float16* ring = reinterpret_cast<_Float16*>(lds);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  const int H = a.H, B = a.B, T = a.T;
-  const int R = (T - 1) * B;
-  const int H4 = 4 * H;
-
-  int ps, mb;                                 // slot of this pass, row block (as k_proj_stream)
-  {
-    const int b = blockIdx.x;
-    if (nslots % 8 == 0) {
-      const int i = b / 8;
-      mb = i % mblocks;
-      ps = (i / mblocks) * 8 + b % 8;
-    } else {
-      ps = b / mblocks;
-      mb = b % mblocks;
-    }
-  }
-  const int sg = ps & 1, pj = ps >> 1;
-  const int e = pj / a.pcs, jl = pj % a.pcs;
-  const int64_t slot = (static_cast<int64_t>(e) * a.PC + jl) * 2 + sg;
-  const float* th = a.theta + static_cast<int64_t>(e) * a.d;
-  const uint2 key = stream_key(a.seeds[e], a.step);
-  const uint32_t pair = static_cast<uint32_t>(a.j0 + jl), step_lo = static_cast<uint32_t>(a.step);
-  const float seps = sg == 0 ? eps_of(a, e, kGroupLstm) : -eps_of(a, e, kGroupLstm);
-  // 32-bit offsets: R 4H floats < 2^31 bytes (host check).  Every DMA offset
-  // is per lane (bounds-checked): row tiles past R (B % 16 == 0) read zeros
-  // and are never stored.
-  const i32x4 hrs = buffer_words(a.hseq + slot * R * H, static_cast<uint32_t>(static_cast<int64_t>(R) * H * 4));
-  const __amdgpu_buffer_rsrc_t gbuf =
-      buffer_of(a.gin + slot * R * H4, static_cast<uint32_t>(static_cast<int64_t>(R) * H4 * sizeof(float)));
-
-  uint4 wh[KC], wl[KC];
-  resident_weights_split<KC, true, kRad, ZW>(wh, wl, reinterpret_cast<float*>(lds), th, a.off_l, a.in_l + H, 0, H,
-                                         mb * 128, a.probe, key, pair, step_lo, seps, a.err);
-
-  // Ring chunk c covers rows [64 (c / NQ), +64) and k [KW (c % NQ), +KW);
-  // block b of it is (part b / (4 QC), row tile (b / QC) % 4, k chunk b % QC).
-  const int nchunks = ((R + 63) / 64) * NQ;
-  auto issue = [&](int c) {
-    const int r0 = (c / NQ) * 64, k0 = (c % NQ) * KW;
-    const uint32_t dst = lds_address(ring + (c & 1) * BUF);
-#pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-      const int b = wave + 8 * i;
-      if (NBLK % 8 == 0 || b < NBLK) {            // wave-uniform
-        const int part = b / (4 * QC), nb = (b / QC) % 4, pq = b % QC;
-        const int rt = r0 / 16 + nb, kc = k0 / 32 + pq;
-        const uint32_t voff = static_cast<uint32_t>((((rt * 2 + part) * KC + kc) * FRAG + lane * 8) * 2);
-        dma16(hrs, voff, 0u, dst + static_cast<uint32_t>(b * FRAG * 2));
-      }
-    }
-  };
-
-  f32x4 acc[4];
-#pragma unroll
-  for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // The weights' probe scratch overlays the ring: the barriers inside the
-  // weight formation come before this first DMA.
-  issue(0);
-  wait_vmem();
-  __syncthreads();
-  for (int c = 0; c < nchunks; ++c) {
-    if (c + 1 < nchunks) issue(c + 1);           // into the buffer chunk c - 1 read
-    const int qq = c % NQ;
-    const _Float16* bl0 = ring + (c & 1) * BUF + lane * 8;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if (q == qq) {                           // compile-time register index into wh, wl
-#pragma unroll
-        for (int pq = 0; pq < QC; ++pq) {
-          uint4 bh[4], bl[4];
-#pragma unroll
-          for (int nb = 0; nb < 4; ++nb) {
-            bh[nb] = *reinterpret_cast<const uint4*>(bl0 + (nb * QC + pq) * FRAG);
-            bl[nb] = *reinterpret_cast<const uint4*>(bl0 + ((4 + nb) * QC + pq) * FRAG);
-          }
-          mfma3_batch<4>(wh[q * QC + pq], wl[q * QC + pq], bh, bl, acc);
-        }
-      }
-    }
-    // The DMA of chunk c + 1 and the stores of the previous tile are done,
-    // every wave's products of chunk c too (its buffer takes chunk c + 2).
-    wait_vmem();
-    __syncthreads();
-    if (qq == NQ - 1) {
-      const int r0 = (c / NQ) * 64;
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        const int row = r0 + nb * 16 + lr;
-        if (row < R) {                        // whole tiles: R % 16 == 0
-          typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-          __builtin_amdgcn_raw_buffer_store_b128(
-              __builtin_bit_cast(u32x4, acc[nb]), gbuf,
-              static_cast<uint32_t>((((r0 / 16 + nb) * mblocks + mb) * 8 + wave) * 1024 + lane * 16), 0, 0);
-        }
-        acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-    }
   }
 }
 

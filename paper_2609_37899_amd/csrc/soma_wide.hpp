@@ -16,16 +16,17 @@
 // A pass of this body runs, for every slot (expert, direction, sign):
 //   k_wide_form   perturbed weights, gains folded into the matrices that
 //                 read a normalised vector, zero-padded to d_p = 64 ceil(d_t
-//                 / 64) and laid out for the kernels below (once per pass)
-//   k_wide_mm     U = E P_in^T (the input projection per byte value)
+//                 / 64), in fragment order (once per pass)
+//   k_wide_split  each expert's E in fragment order
+//   k_mm          U = E P_in^T (the input projection per byte value)
 //   k_wide_ln     x = U[byte], n = LN(x)   (the gain sits in the weights)
-//   per block:    k_wide_mm gin = n A'      (gate inputs, units interleaved)
-//                 k_rec_persist h           (recurrent weights pre-formed)
+//   per block:    k_mm gin = n A'           (gate inputs, units interleaved)
+//                 k_rec_xchg or k_rec_persist h   (recurrent weights pre-formed)
 //                 k_wide_ln x += h, n = LN(x)
-//                 k_wide_mm m = GELU(n U')
-//                 k_wide_mm x += m V^T
+//                 k_mm m = GELU(n U')
+//                 k_mm x += m V^T
 //   k_wide_ln     n = LN(x)
-//   k_wide_mm     u = n P_out'^T (the final gain folded into P_out)
+//   k_mm          u = n P_out'^T (the final gain folded into P_out)
 //   k_wide_head   logits = u E^T, cross entropy
 // Padded units have zero weights and zero gate inputs, so their cell state
 // and h stay exactly 0 and every padded column of x stays 0.
@@ -33,6 +34,7 @@
 
 #include "soma_kernels.hpp"
 #include "soma_body.hpp"
+#include "soma_mm.hpp"
 
 namespace soma {
 
@@ -49,10 +51,9 @@ struct WideForm {
 __host__ __device__ inline WideForm wide_form_layout(int dp, int D) {
   WideForm f{};
   const int64_t m = 4 * int64_t(dp) * dp;
-  // Every matrix is stored output-major and split, [n][2][k] halves (a
-  // row's hi parts, then its lo parts: the bytes of the fp32 matrix): the
-  // rows of the gate matrices are interleaved (row 4 u + g is gate g of
-  // unit u).
+  // Every matrix is stored output-major, split and in fragment order (the
+  // bytes of the fp32 matrix): the rows of the gate matrices are interleaved
+  // (row 4 u + g is gate g of unit u).
   f.pin = 0;                                   // P_in   [d_p][32]
   f.blk0 = int64_t(dp) * kWideHeadWidth;       // per block: A' [4 d_p][d_p], R [4 d_p][d_p],
   f.blk_stride = 4 * m;                        //   U' [4 d_p][d_p], V [d_p][4 d_p]
@@ -70,7 +71,7 @@ struct WideArgs {
   float* wform;           // pre-formed weights, [slots][WideForm::total]
   float* U;               // [slots][256][d_p]
   float* x;               // [slots][R][d_p] residual stream
-  float* n;               // [slots][R][d_p] normalised x, split (also h of the recurrence, fp32)
+  float* n;               // [slots][ceil(R / 16) 16][d_p] normalised x in fragment order (also h of the recurrence, fp32)
   float* gin;             // [slots][R][4 d_p] gate inputs, then the MLP hidden layer
   double* part;           // [slots][row_tiles] cross-entropy sums
   float* fdec;            // evaluation: decoder inputs u [N][B][T-1][32] (position b (T-1) + t)
@@ -110,14 +111,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One fp32 value -> its fp16 parts, as split2 does for a pair (hi rounded
-// toward zero, lo the exact remainder rounded toward zero).
-__device__ __forceinline__ void split1(float v, _Float16& hi, _Float16& lo) {
-  const auto h = __builtin_amdgcn_cvt_pkrtz(v, 0.0f);
-  hi = h[0];
-  lo = __builtin_amdgcn_cvt_pkrtz(v - static_cast<float>(h[0]), 0.0f)[0];
-}
-
 // Slot s of the pass: (expert, direction in the pass, sign).
 __device__ __forceinline__ void wide_slot(const WideArgs& a, int s, int& e, int& jl, int& sg) {
   sg = s % a.NS;
@@ -142,83 +135,131 @@ __device__ __forceinline__ float wide_coord(const float* th, int64_t k, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Pre-formed weights of every slot: one canonical probe quad per thread
-// (grid: quads of the matrices, slots).  The gains are not stored: each
-// matrix quad that reads a normalised vector multiplies by the perturbed gain
-// of its row (one more probe quad).  Padded entries are zeroed beforehand
-// (k_fill_f32).  A formed weight outside the split products' range, or NaN,
-// sets the step's abort flag.
+// Pre-formed weights of every slot, in fragment order.  A thread forms 16-byte
+// words, so that stores are words and not halves:
+//  * matrices whose canonical rows run along K's other side (A, R, U [c][j] and
+//    P_out [c][q]; K index c): eight rows c of one column quad, i.e. eight
+//    probe quads, giving one hi and one lo word for each of its four columns
+//    (blockIdx.y: matrix and group of eight rows);
+//  * V [c][j] and P_in [c][q] (K index j, q): eight columns of one row, two
+//    quads, one hi and one lo word.
+// The gains are not stored: the matrices that read a normalised vector
+// multiply by the perturbed gain of their K index (drawn once per block).
+// Padded entries are zeroed beforehand (k_fill_f32) or written as zeros.  A
+// formed weight outside the split products' range, or NaN, sets the step's
+// abort flag.
 // ---------------------------------------------------------------------------
+constexpr int kFormThreads = 128;
+
+// Row groups along c, and the rows of blockIdx.y: 3 D matrices (A, R, U of
+// each block) and P_out by groups of eight c, then V and P_in by rows c.
+__host__ __device__ inline int wide_form_groups(int dt) { return (dt + 7) / 8; }
+__host__ __device__ inline int wide_form_rows(int dt, int D) {
+  return (3 * D + 1) * wide_form_groups(dt) + (D + 1) * dt;
+}
+
 template <bool kPert>
-__global__ __launch_bounds__(256) void k_wide_form(WideArgs a) {
+__global__ __launch_bounds__(kFormThreads) void k_wide_form(WideArgs a) {
+  __shared__ float gains[8];
   const int dt = a.dt, dp = a.dp, D = a.D;
   const int64_t dt4 = 4 * int64_t(dt), mat = dt4 * dt;
   const int64_t blk0 = int64_t(dt) * kWideHeadWidth, pout0 = blk0 + D * 4 * mat;
   const int64_t gain0 = pout0 + int64_t(dt) * kWideHeadWidth;
-  const int64_t k = 4 * (blockIdx.x * int64_t(blockDim.x) + threadIdx.x);
-  if (k >= gain0) return;
   int e, jl, sg;
-  wide_slot(a, blockIdx.y, e, jl, sg);
+  wide_slot(a, blockIdx.z, e, jl, sg);
   const int64_t slot = wide_slot_index(a, e, jl, sg);
   const float* th = a.theta + int64_t(e) * a.d;
   const uint2 key = kPert ? stream_key(a.seeds[e], a.step) : make_uint2(0u, 0u);
   const uint32_t pair = static_cast<uint32_t>(a.j0 + jl), step_lo = static_cast<uint32_t>(a.step);
   const float eps = kPert ? a.eps_v[int64_t(e) * a.eps_stride] : 0.0f;
   const float seps = sg == 0 ? eps : -eps;
-  float w[4];
-  if (kPert) {
-    const int lw = a.probe;   // matrices follow the configured law
-    const float4 z = probe_quad(lw, key, pair, step_lo, static_cast<uint64_t>(k));
-    w[0] = __builtin_fmaf(seps, z.x, th[k]);
-    w[1] = __builtin_fmaf(seps, z.y, th[k + 1]);
-    w[2] = __builtin_fmaf(seps, z.z, th[k + 2]);
-    w[3] = __builtin_fmaf(seps, z.w, th[k + 3]);
-  } else {
-    w[0] = th[k]; w[1] = th[k + 1]; w[2] = th[k + 2]; w[3] = th[k + 3];
-  }
+  // The perturbed canonical quad at k (a multiple of 4).
+  auto quad = [&](int64_t k) {
+    const float4 t = make_float4(th[k], th[k + 1], th[k + 2], th[k + 3]);
+    return kPert ? fma4(seps, probe_quad(a.probe, key, pair, step_lo, static_cast<uint64_t>(k)), t) : t;
+  };
   const WideForm F = wide_form_layout(dp, D);
   _Float16* out = reinterpret_cast<_Float16*>(a.wform + slot * F.total);
   bool ok = true;
-  // Element (row, col) of a matrix at float offset base with rows of K
-  // values, stored split: row r is K hi parts then K lo parts.
-  auto put = [&](int64_t base, int64_t row, int64_t col, int64_t K, float v) {
-    ok = ok && __builtin_fabsf(v) <= kSplitMax;
-    _Float16 h, l;
-    split1(v, h, l);
-    _Float16* p = out + 2 * base + row * 2 * K + col;
-    p[0] = h;
-    p[K] = l;
+  // Eight values k .. k + 7 of row `row` of the matrix at element offset base with K columns.
+  auto put = [&](int64_t base, int row, int k, int K, const float4& x, const float4& y) {
+    ok = ok && split_range_ok(x) && split_range_ok(y);
+    uint4 hi, lo;
+    split8v(x, y, hi, lo);
+    _Float16* w = out + 2 * base + (int64_t(row >> 4) * 2 * (K / 32) + (k >> 5)) * 512 +
+                  (16 * ((k >> 3) & 3) + (row & 15)) * 8;
+    *reinterpret_cast<uint4*>(w) = hi;
+    *reinterpret_cast<uint4*>(w + (K / 32) * 512) = lo;
   };
-  if (k < blk0) {                                     // P_in [c][q]
-    const int64_t c = k / kWideHeadWidth, q = k % kWideHeadWidth;
-    for (int i = 0; i < 4; ++i) put(F.pin, c, q + i, kWideHeadWidth, w[i]);
-  } else if (k < pout0) {
-    const int64_t r = k - blk0;
-    const int l = static_cast<int>(r / (4 * mat));
-    const int which = static_cast<int>((r / mat) % 4);
-    const int64_t rr = r % mat, c = rr / dt4, j = rr % dt4;
-    const int64_t mp = 4 * int64_t(dp) * dp, base = F.blk0 + l * F.blk_stride + which * mp;
-    float g = 1.0f;
-    if (which == 0 || which == 2)                     // A reads LN(x; g1), U reads LN(x; g2)
-      g = wide_coord(th, gain0 + (2 * l + (which == 2 ? 1 : 0)) * int64_t(dt) + c, gain0, a.probe, key, pair,
-                     step_lo, seps);
-    for (int i = 0; i < 4; ++i) {
-      const int64_t jj = j + i;
-      if (which <= 1) {                               // gate column g dt + u -> row 4 u + g (A' and R)
-        const int64_t gate = jj / dt, u = jj % dt;
-        put(base, 4 * u + gate, c, dp, which == 0 ? w[i] * g : w[i]);
-      } else if (which == 2) {                        // U'[j][c]
-        put(base, jj, c, dp, w[i] * g);
-      } else {                                        // V[c][j]: row = output feature
-        put(base, c, jj, 4 * int64_t(dp), w[i]);
+  const int groups = wide_form_groups(dt);
+  const int i = blockIdx.x * kFormThreads + threadIdx.x;
+  int y = blockIdx.y;
+  if (y < (3 * D + 1) * groups) {                       // block-uniform
+    const int mi = y / groups, c0 = 8 * (y % groups);
+    const bool is_out = mi == 3 * D;
+    const int l = mi / 3, which = is_out ? 0 : mi % 3;  // A, R, U
+    const bool gained = is_out || which != 1;           // A reads LN(x; g1), U LN(x; g2), P_out LN(x; g_f)
+    if (threadIdx.x < 8) {
+      float g = 1.0f;
+      const int64_t gk = gain0 + (is_out ? 2 * D : 2 * l + (which == 2 ? 1 : 0)) * int64_t(dt) + c0 + threadIdx.x;
+      if (gained && c0 + static_cast<int>(threadIdx.x) < dt)
+        g = wide_coord(th, gk, gain0, a.probe, key, pair, step_lo, seps);
+      gains[threadIdx.x] = g;
+    }
+    __syncthreads();
+    const int ncol = is_out ? kWideHeadWidth : 4 * dt;
+    const int j = 4 * i;
+    if (j < ncol) {
+      const int64_t src = is_out ? pout0 : blk0 + l * 4 * mat + which * mat;
+      float v[8][4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (c0 + r < dt) w = quad(src + int64_t(c0 + r) * ncol + j);
+        const float g = gains[r];
+        v[r][0] = w.x * g; v[r][1] = w.y * g; v[r][2] = w.z * g; v[r][3] = w.w * g;
+      }
+      const int64_t base = is_out ? F.pout : F.blk0 + l * F.blk_stride + which * (4 * int64_t(dp) * dp);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int jj = j + q;
+        // gate column g d_t + u -> row 4 u + g (A' and R); U' and P_out': row j
+        const int row = !is_out && which <= 1 ? 4 * (jj % dt) + jj / dt : jj;
+        put(base, row, c0, dp, make_float4(v[0][q], v[1][q], v[2][q], v[3][q]),
+            make_float4(v[4][q], v[5][q], v[6][q], v[7][q]));
       }
     }
-  } else {                                            // P_out'[q][c] = P_out[c][q] g_f[c]
-    const int64_t r = k - pout0, c = r / kWideHeadWidth, q = r % kWideHeadWidth;
-    const float g = wide_coord(th, gain0 + 2 * int64_t(D) * dt + c, gain0, a.probe, key, pair, step_lo, seps);
-    for (int i = 0; i < 4; ++i) put(F.pout, q + i, c, dp, w[i] * g);
+  } else {
+    y -= (3 * D + 1) * groups;
+    const int l = y / dt, c = y % dt;                   // V of block l, or P_in (l == D)
+    const bool is_in = l == D;
+    const int K = is_in ? kWideHeadWidth : 4 * dt, j = 8 * i;
+    if (j < K) {
+      const int64_t src = (is_in ? 0 : blk0 + l * 4 * mat + 3 * mat) + int64_t(c) * K + j;
+      const float4 x = quad(src);
+      const float4 w = j + 4 < K ? quad(src + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const int64_t base = is_in ? F.pin : F.blk0 + l * F.blk_stride + 3 * (4 * int64_t(dp) * dp);
+      put(base, c, j, is_in ? kWideHeadWidth : 4 * dp, x, w);
+    }
   }
   report_split_range(a.err, ok);
+}
+
+// Each expert's tied matrix E [256][32] in fragment order (256 x 32 split
+// pairs at esplit + expert * 8192): one word per thread, one expert per
+// blockIdx.y.
+__global__ __launch_bounds__(256) void k_wide_split(const float* E, int64_t e_stride, float* esplit, unsigned* err) {
+  constexpr int K = kWideHeadWidth;
+  const int i = blockIdx.x * 256 + threadIdx.x, row = i >> 2, g = i & 3;   // 4 words of hi a row
+  const float* src = E + int64_t(blockIdx.y) * e_stride + row * K + 8 * g;
+  const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
+  uint4 hi, lo;
+  split8v(x, y, hi, lo);
+  _Float16* w = reinterpret_cast<_Float16*>(esplit + int64_t(blockIdx.y) * kVocab * K) + int64_t(row >> 4) * 2 * 512 +
+                (16 * g + (row & 15)) * 8;
+  *reinterpret_cast<uint4*>(w) = hi;
+  *reinterpret_cast<uint4*>(w + 512) = lo;
+  report_split_range(err, split_range_ok(x) && split_range_ok(y));
 }
 
 // out[i] = 0 for i < n (a fill kernel, so that callers may capture it).
@@ -228,246 +269,112 @@ __global__ void k_fill_f32(float* out, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// Batched products on the fp16 matrix cores from split fp32 operands:
-//   C[s][m][n] (= | += | GELU of) sum_k A[s][m][k] W[s][n][k]
-// W is stored split ([N][2][K] halves: per row its K hi parts, then its K lo
-// parts), as the form kernel writes it.  A is either stored split the same
-// way ([M][2][K], written so by LayerNorm and by the GELU epilogue) or fp32
-// [M][K], split as it is staged (the tied matrix of the input projection);
-// per slot, or per expert.  C is fp32 [M][N] (store, add), split [M][2][N]
-// (GELU: the next product's A), or the tiled gate inputs of the exchange
-// recurrence (gates: rows t B + b).  Block tile 128 (n) x 128 (m),
-// four waves of 64 x 64; K in 32-wide chunks (K % 32 == 0, N % 4 == 0)
-// staged through two LDS buffers: chunk c + 1's global loads are in flight
-// during chunk c's products and stored into the other buffer after them,
-// one block barrier per chunk.  Tiles are dealt so that each XCD (blocks go to
-// the 8 XCDs round-robin) works through a contiguous range of them: the n
-// tiles of one m tile, and the m tiles of one slot, share its L2.
-// ---------------------------------------------------------------------------
-enum WideEpi { kEpiStore = 0, kEpiGelu = 1, kEpiAdd = 2, kEpiGates = 3 };
-
-struct MmArgs {
-  const void* A;
-  int64_t a_slot;     // A elements (floats or split pairs) between consecutive A matrices (slots, or experts)
-  int a_expert;       // A is per expert rather than per slot
-  const void* W;      // split
-  int64_t w_slot;     // floats (split pairs) between slots' matrices
-  void* C;
-  int64_t c_slot;     // elements between slots' outputs
-  int M, N, K;
-  int pcs, PC, NS;    // the pass's slots
-  int ntn, ntm;       // n tiles, m tiles
-  int B;              // sequences (kEpiGates: row m is sequence m % B of step m / B)
-  int64_t tiles;      // ntn * ntm * slots
-  unsigned* err;
-};
-
-constexpr int kMmLd = 80;   // LDS row in halves: 32 hi, 32 lo, 16 spare (160 bytes, an odd multiple of 32)
-constexpr int kXcds = 8;
-
-template <bool kASplit, int kEpi>
-__global__ __launch_bounds__(256) void k_wide_mm(MmArgs p) {
-  __shared__ __attribute__((aligned(16))) _Float16 sa[2][128 * kMmLd];   // [buffer] activations, rows hi | lo
-  __shared__ __attribute__((aligned(16))) _Float16 sw[2][128 * kMmLd];   // [buffer] weights, rows hi | lo
-  const int64_t per_xcd = (p.tiles + kXcds - 1) / kXcds;
-  const int64_t tile = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-  if (tile >= p.tiles) return;                          // block-uniform
-  const int nt = static_cast<int>(tile % p.ntn);
-  const int64_t rest = tile / p.ntn;
-  const int mtile = static_cast<int>(rest % p.ntm), z = static_cast<int>(rest / p.ntm);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-  const int wn = wave & 1, wm = wave >> 1;
-  const int n0 = nt * 128, m0 = mtile * 128;
-  const int sg = z % p.NS, jl = (z / p.NS) % p.pcs, e = z / (p.NS * p.pcs);
-  const int64_t s = (int64_t(e) * p.PC + jl) * p.NS + sg;
-  const int64_t a_off = (p.a_expert ? int64_t(e) : s) * p.a_slot;
-  const int M = p.M, N = p.N, K = p.K;
-  const _Float16* Wh = reinterpret_cast<const _Float16*>(p.W) + 2 * s * p.w_slot;
-  bool ok = true;
-
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Staging: a split row chunk is 32 hi then 32 lo halves (4 uint4 each);
-  // an fp32 row chunk is 8 float4.  Thread idx = t + 256 i covers row
-  // idx >> 3 and piece idx & 7 of both operands.
-  uint4 pa[4], pw[4];
-  float4 pf[4];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = threadIdx.x + 256 * i;
-      const int row = idx >> 3, pc = idx & 7, part = pc >> 2, q = pc & 3;
-      const int m = m0 + row, n = n0 + row;
-      if constexpr (kASplit) {
-        const _Float16* A = reinterpret_cast<const _Float16*>(p.A) + 2 * a_off;
-        pa[i] = m < M ? *reinterpret_cast<const uint4*>(A + int64_t(m) * 2 * K + part * K + k0 + 8 * q)
-                      : make_uint4(0u, 0u, 0u, 0u);
-      } else {
-        const float* A = reinterpret_cast<const float*>(p.A) + a_off;
-        pf[i] = m < M ? *reinterpret_cast<const float4*>(A + int64_t(m) * K + k0 + 4 * pc)
-                      : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      pw[i] = n < N ? *reinterpret_cast<const uint4*>(Wh + int64_t(n) * 2 * K + part * K + k0 + 8 * q)
-                    : make_uint4(0u, 0u, 0u, 0u);
-    }
-  };
-  auto sstore = [&](int b) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = threadIdx.x + 256 * i;
-      const int row = idx >> 3, pc = idx & 7, part = pc >> 2, q = pc & 3;
-      if constexpr (kASplit) {
-        *reinterpret_cast<uint4*>(&sa[b][row * kMmLd + 32 * part + 8 * q]) = pa[i];
-      } else {
-        uint2 hi, lo;
-        ok = ok && split_range_ok(pf[i]);
-        split4(pf[i], hi, lo);
-        *reinterpret_cast<uint2*>(&sa[b][row * kMmLd + 4 * pc]) = hi;
-        *reinterpret_cast<uint2*>(&sa[b][row * kMmLd + 32 + 4 * pc]) = lo;
-      }
-      *reinterpret_cast<uint4*>(&sw[b][row * kMmLd + 32 * part + 8 * q]) = pw[i];
-    }
-  };
-
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  const int nk = K / 32;
-  for (int c = 0; c < nk; ++c) {
-    const int b = c & 1;
-    if (c + 1 < nk) gload(32 * (c + 1));
-    uint4 bh[4], bl[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int row = wm * 64 + 16 * mt + lr;
-      bh[mt] = *reinterpret_cast<const uint4*>(&sa[b][row * kMmLd + 8 * lg]);
-      bl[mt] = *reinterpret_cast<const uint4*>(&sa[b][row * kMmLd + 32 + 8 * lg]);
-    }
-#pragma unroll
-    for (int ntl = 0; ntl < 4; ++ntl) {
-      const int row = wn * 64 + 16 * ntl + lr;
-      const uint4 wh = *reinterpret_cast<const uint4*>(&sw[b][row * kMmLd + 8 * lg]);
-      const uint4 wl = *reinterpret_cast<const uint4*>(&sw[b][row * kMmLd + 32 + 8 * lg]);
-      mfma3_batch<4>(wh, wl, bh, bl, acc[ntl]);
-    }
-    // The other buffer was last read in chunk c - 1, before the barrier
-    // that ended it.
-    if (c + 1 < nk) sstore(b ^ 1);
-    __syncthreads();
-  }
-
-  // acc[ntl][mt][i] = C[m0 + 64 wm + 16 mt + lr][n0 + 64 wn + 16 ntl + 4 lg + i]
-#pragma unroll
-  for (int ntl = 0; ntl < 4; ++ntl) {
-    const int n = n0 + wn * 64 + 16 * ntl + 4 * lg;
-    if (n >= N) continue;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m = m0 + wm * 64 + 16 * mt + lr;
-      if (m >= M) continue;
-      float4 v = make_float4(acc[ntl][mt][0], acc[ntl][mt][1], acc[ntl][mt][2], acc[ntl][mt][3]);
-      if constexpr (kEpi == kEpiGelu) {
-        v = make_float4(gelu_f(v.x), gelu_f(v.y), gelu_f(v.z), gelu_f(v.w));
-        ok = ok && split_range_ok(v);
-        uint2 hi, lo;
-        split4(v, hi, lo);
-        _Float16* C = reinterpret_cast<_Float16*>(p.C) + 2 * s * p.c_slot + int64_t(m) * 2 * N + n;
-        *reinterpret_cast<uint2*>(C) = hi;
-        *reinterpret_cast<uint2*>(C + N) = lo;
-      } else if constexpr (kEpi == kEpiGates) {
-        const int t = m / p.B, b = m - t * p.B, RT = (p.B + 15) / 16;
-        const int64_t off = ((int64_t(t * RT + (b >> 4)) * (N / 128) + (n >> 7)) * 8 + ((n >> 4) & 7)) * 256 +
-                            ((b & 15) + 16 * ((n >> 2) & 3)) * 4;
-        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + s * p.c_slot + off) = v;
-      } else {
-        float4* c = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.C) + s * p.c_slot + int64_t(m) * N + n);
-        if constexpr (kEpi == kEpiAdd) {
-          const float4 o = *c;
-          v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
-        }
-        *c = v;
-      }
-    }
-  }
-  report_split_range(p.err, ok);
-}
-
-// ---------------------------------------------------------------------------
-// Gain-free LayerNorm of every row of x, one wave per row (four per block):
+// Gain-free LayerNorm of every row of x, a row tile of 16 per block, four rows
+// a wave one after another:
 //   kMode 0: x = U[byte]          (the embedding's projection per byte value)
 //   kMode 1: x += h               (the LSTM sublayer's residual; h in n)
 //   kMode 2: x as it is
 // then n = (x - mean) / sqrt(var + 1e-5) over the first d_t features (biased
-// variance), 0 on the padded ones, written split (the row's hi parts, then
-// its lo parts) over the fp32 row of h it replaces.  Rows are r = t B + b.
+// variance), 0 on the padded ones and on rows past the last, gathered in LDS
+// and written in fragment order over the 16 fp32 rows of h it replaces (read by
+// this block alone, before its barrier).  Rows are r = t B + b.
 // ---------------------------------------------------------------------------
 template <int kMode>
 __global__ __launch_bounds__(256) void k_wide_ln(WideArgs a) {
   constexpr int kMaxC = 8;   // d_p <= 512
+  constexpr int LD = 64 * kMaxC + 4;                    // LDS row in split pairs
+  __shared__ uint32_t tile[16][LD];                     // (hi, lo) of every value
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t R = int64_t(a.T - 1) * a.B;
-  const int64_t r = int64_t(blockIdx.x) * 4 + wave;
-  if (r >= R) return;
+  const int64_t r0 = int64_t(blockIdx.x) * 16;
   const int s = blockIdx.y;
   int e, jl, sg;
   wide_slot(a, s, e, jl, sg);
   const int64_t slot = wide_slot_index(a, e, jl, sg);
   const int dp = a.dp, dt = a.dt, nc = dp / 64;
-  float* xr = a.x + (slot * R + r) * dp;
-  float* nr = a.n + (slot * R + r) * dp;
-  float v[kMaxC];
-  if (kMode == 0) {
-    const int64_t t = r / a.B, b = r % a.B;
-    const uint8_t* by = a.bytes + int64_t((a.j0 + jl) / a.ppb) * a.bstride + (int64_t(e) * a.B + b) * a.T;
-    const float* ur = a.U + (slot * kVocab + by[t]) * dp;
+  const int64_t n_rows = (R + 15) / 16 * 16;
+  // The wave's rows are all requested before the first is used.
+  float v[4][kMaxC];
+#pragma unroll
+  for (int rr = 0; rr < 4; ++rr) {
+    const int64_t r = r0 + wave * 4 + rr;
+#pragma unroll
+    for (int i = 0; i < kMaxC; ++i) v[rr][i] = 0.0f;
+    if (r >= R) continue;                               // wave-uniform
+    const float* src = a.x + (slot * R + r) * dp;
+    if (kMode == 0) {
+      const int64_t t = r / a.B, b = r % a.B;
+      const uint8_t* by = a.bytes + int64_t((a.j0 + jl) / a.ppb) * a.bstride + (int64_t(e) * a.B + b) * a.T;
+      src = a.U + (slot * kVocab + by[t]) * dp;
+    }
 #pragma unroll
     for (int i = 0; i < kMaxC; ++i)
-      if (i < nc) {
-        v[i] = ur[64 * i + lane];
-        xr[64 * i + lane] = v[i];
+      if (i < nc) v[rr][i] = src[64 * i + lane];
+  }
+  if (kMode == 1) {
+    float h[4][kMaxC];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const int64_t r = r0 + wave * 4 + rr;
+      const float* nr = a.n + (slot * n_rows + r) * dp;
+#pragma unroll
+      for (int i = 0; i < kMaxC; ++i) h[rr][i] = i < nc && r < R ? nr[64 * i + lane] : 0.0f;
+    }
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+      for (int i = 0; i < kMaxC; ++i) v[rr][i] += h[rr][i];
+  }
+#pragma unroll
+  for (int rr = 0; rr < 4; ++rr) {
+    const int row = wave * 4 + rr;
+    const int64_t r = r0 + row;
+    if (kMode != 2 && r < R) {
+      float* xr = a.x + (slot * R + r) * dp;
+#pragma unroll
+      for (int i = 0; i < kMaxC; ++i)
+        if (i < nc) xr[64 * i + lane] = v[rr][i];
+    }
+    float sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMaxC; ++i)
+      if (i < nc && 64 * i + lane < dt) sum += v[rr][i];
+    sum = wave_sum(sum);
+    const float mean = sum / static_cast<float>(dt);
+    float sq = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMaxC; ++i)
+      if (i < nc && 64 * i + lane < dt) {
+        const float c = v[rr][i] - mean;
+        sq = __builtin_fmaf(c, c, sq);
       }
-  } else {
+    sq = wave_sum(sq);
+    const float inv = 1.0f / __builtin_sqrtf(sq / static_cast<float>(dt) + 1e-5f);
 #pragma unroll
     for (int i = 0; i < kMaxC; ++i)
       if (i < nc) {
-        v[i] = xr[64 * i + lane];
-        if (kMode == 1) {
-          v[i] += nr[64 * i + lane];
-          xr[64 * i + lane] = v[i];
-        }
+        const float y = 64 * i + lane < dt && r < R ? (v[rr][i] - mean) * inv : 0.0f;
+        uint32_t hi, lo;
+        split2(y, 0.0f, hi, lo);
+        tile[row][64 * i + lane] = (hi & 0xFFFFu) | (lo << 16);
       }
   }
-  float sum = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kMaxC; ++i)
-    if (i < nc && 64 * i + lane < dt) sum += v[i];
-  sum = wave_sum(sum);
-  const float mean = sum / static_cast<float>(dt);
-  float sq = 0.0f;
-#pragma unroll
-  for (int i = 0; i < kMaxC; ++i)
-    if (i < nc && 64 * i + lane < dt) {
-      const float c = v[i] - mean;
-      sq = __builtin_fmaf(c, c, sq);
-    }
-  sq = wave_sum(sq);
-  const float inv = 1.0f / __builtin_sqrtf(sq / static_cast<float>(dt) + 1e-5f);
-  // n, split into its fp16 parts: the row's dp hi parts, then its dp lo
-  // parts (the bytes of the fp32 row it replaces).
-  _Float16* ns = reinterpret_cast<_Float16*>(nr);
-#pragma unroll
-  for (int i = 0; i < kMaxC; ++i)
-    if (i < nc) {
-      const float y = 64 * i + lane < dt ? (v[i] - mean) * inv : 0.0f;
-      _Float16 h, l;
-      split1(y, h, l);
-      ns[64 * i + lane] = h;
-      ns[dp + 64 * i + lane] = l;
-    }
+  __syncthreads();
+  // Word w of the tile's d_p / 32 chunks: chunk w >> 6, word w & 63 of its hi
+  // and lo blocks.
+  _Float16* dst = reinterpret_cast<_Float16*>(a.n + (slot * n_rows + r0) * dp);
+  const int KC = dp / 32;
+  for (int w = threadIdx.x; w < KC * 64; w += 256) {
+    const int kc = w >> 6, row = w & 15, g = (w >> 4) & 3;
+    const uint4 p0 = *reinterpret_cast<const uint4*>(&tile[row][32 * kc + 8 * g]);
+    const uint4 p1 = *reinterpret_cast<const uint4*>(&tile[row][32 * kc + 8 * g + 4]);
+    const uint4 hi = make_uint4((p0.x & 0xFFFFu) | (p0.y << 16), (p0.z & 0xFFFFu) | (p0.w << 16),
+                                (p1.x & 0xFFFFu) | (p1.y << 16), (p1.z & 0xFFFFu) | (p1.w << 16));
+    const uint4 lo = make_uint4((p0.x >> 16) | (p0.y & 0xFFFF0000u), (p0.z >> 16) | (p0.w & 0xFFFF0000u),
+                                (p1.x >> 16) | (p1.y & 0xFFFF0000u), (p1.z >> 16) | (p1.w & 0xFFFF0000u));
+    *reinterpret_cast<uint4*>(dst + kc * 512 + (w & 63) * 8) = hi;
+    *reinterpret_cast<uint4*>(dst + (KC + kc) * 512 + (w & 63) * 8) = lo;
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -46,10 +46,10 @@ namespace soma {
 //    8 lg .. + 7 -- row group lg's eight units, brought into one lane by lane
 //    swaps, so a wave stores whole 128-byte lines straight from the cell
 //    lanes.  A group keeps two steps per tile (parity t mod 2) in L2.  h_t
-//    also goes to the layer's hseq rows for the kernels that read the whole
-//    sequence: in fp32, or (split_out: B % 16 == 0, where the next layer's
-//    projection is k_proj_dma) as the same split words, in 1 KiB blocks
-//    [16-row tile][hi, lo][32-wide k chunk].
+//    also goes to the layer's hseq for the kernels that read the whole
+//    sequence: in fp32 rows, or (split_out, where the next layer's projection
+//    is k_mm) as the same split words, in fragment order, every time step in
+//    whole row tiles (rows past the batch are finite and used by nobody).
 //  * The tile's h_{t-1} reaches LDS by DMA (buffer_load_dwordx4 ... lds):
 //    each 1 KiB block lands unchanged.  The DMA of sub-step s + 2 is issued
 //    after the block barrier that ends the products of sub-step s, into the
@@ -131,13 +131,6 @@ __device__ __forceinline__ void resident_weights_khalf(uint4 (&wh)[2][NCH], uint
   __syncthreads();
 }
 
-// Waits until at most N of this wave's memory accesses are outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vmem_but() {
-  static_assert(N < 16, "");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
-}
-
 // kL1: the layer reads its inputs from the folded table by byte value (layer
 // 1) rather than from the time-parallel gate inputs; kPre: the recurrent
 // weights come pre-formed (a.wpre), a pass may run one sign per direction
@@ -213,7 +206,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int64_t H4 = 4 * static_cast<int64_t>(H);
   const int RT = (B + 15) / 16;                         // row tiles of a time step
   const int64_t gin_rows = static_cast<int64_t>(T - 1) * RT * 16;
-  const uint32_t slot_bytes = static_cast<uint32_t>(R * H * sizeof(float));   // < 2^31 (host check)
+  const uint32_t slot_bytes = static_cast<uint32_t>((p.split_out ? gin_rows : R) * H * sizeof(float));   // < 2^31 (host check)
   constexpr int kGiChunk = NCH / 2;                     // chunk after which the next inputs are requested
   constexpr uint32_t kOut = 0x80000000u;                // past every buffer: a store there is dropped
   bool failed = false;                                  // this wave stopped waiting (abort)
@@ -240,6 +233,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
 
   const bool one_sign = kPre && a.ns == 1;
+  const int seq_step = p.split_out ? RT * 16 : B;       // rows of a time step in hseq
   const uint32_t split_mask = p.split_out ? 0xFFFFFFFFu : 0u;
   // Published word of this lane's row (lane groups 0, 1: the hi and lo word
   // for the ring; 2, 3: the same, or in fp32 the two unit quads, for the
@@ -431,13 +425,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         v2 = __hip_atomic_load(flags + k2 * 64 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_sched_barrier(0);
         // The layer's sequence, last: it is not waited for.  A select without
-        // a branch; rows past the batch are dropped (fp32 rows; the split
-        // layout is used with whole tiles).
+        // a branch; fp32 rows past the batch, and split row tiles past the
+        // time step's, are dropped.
         const float4 q = odd ? hv[1] : hv[0];
         const u32x4 fp = {__float_as_uint(q.x), __float_as_uint(q.y), __float_as_uint(q.z), __float_as_uint(q.w)};
         const u32x4 sv = (words & split_mask) | (fp & ~split_mask);
-        const uint32_t off = lg >= 2 && k * 16 + lr < nrows
-                                 ? seq_lane + static_cast<uint32_t>((t * B + k * 16) * H * 4)   // the same in both layouts
+        const uint32_t off = lg >= 2 && k * 16 + (p.split_out ? 0 : lr) < nrows
+                                 ? seq_lane + static_cast<uint32_t>((t * seq_step + k * 16) * H * 4)
                                  : kOut;
         __builtin_amdgcn_raw_buffer_store_b128(sv, hbuf, off, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
@@ -528,7 +522,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int sg = one_sign ? 0 : sj & 1, pj = one_sign ? sj : sj >> 1;
     const int e = pj / a.pcs, jl = pj % a.pcs;
     const int64_t slot = (static_cast<int64_t>(e) * a.PC + jl) * (one_sign ? 1 : 2) + sg;
-    const __amdgpu_buffer_rsrc_t hbuf = buffer_of(a.hseq + slot * R * H, slot_bytes);
+    const __amdgpu_buffer_rsrc_t hbuf = buffer_of(a.hseq + slot * a.hrows * H, slot_bytes);
     const __amdgpu_buffer_rsrc_t gbuf =
         kL1 ? buffer_of(a.U + slot * kVocab * H4, static_cast<uint32_t>(kVocab * H4 * sizeof(float)))
             : buffer_of(a.gin + slot * gin_rows * H4, static_cast<uint32_t>(gin_rows * H4 * sizeof(float)));
@@ -544,15 +538,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // inside order it after the previous job's last fragment reads).
     uint4 wh[2][NCH], wl[2][NCH];
     if constexpr (kPre) {
-      // Rows of the pre-formed matrix: a row's H hi parts, then its H lo parts.
+      // Fragments as the pre-formed matrix stores them (soma_mm.hpp).
 #pragma unroll
       for (int m = 0; m < 2; ++m) {
         const _Float16* wr = reinterpret_cast<const _Float16*>(a.wpre + slot * a.wpre_slot) +
-                             static_cast<int64_t>(utile * 128 + 32 * rg + 16 * m + lr) * 2 * H + 32 * kh * NCH + 8 * lg;
+                             (static_cast<int64_t>(utile * 8 + 2 * rg + m) * 2 * KC + kh * NCH) * FRAG + lane * 8;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-          wh[m][c] = *reinterpret_cast<const uint4*>(wr + 32 * c);
-          wl[m][c] = *reinterpret_cast<const uint4*>(wr + H + 32 * c);
+          wh[m][c] = *reinterpret_cast<const uint4*>(wr + c * FRAG);
+          wl[m][c] = *reinterpret_cast<const uint4*>(wr + (KC + c) * FRAG);
         }
       }
     } else {

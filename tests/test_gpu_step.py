@@ -217,7 +217,7 @@ def test_local_recurrence_is_repeatable(name, probe):
 @pytest.mark.parametrize("name,probe", [("b64_h128", 0), ("b64_h128", 2), ("h256_b64_jobs", 1)])
 def test_presplit_sequence_is_bit_identical(name, probe):
     """Layer 1's exchange recurrence stores its h pre-split in fragment order
-    and layer 2's projection stages it by DMA (k_proj_dma); with
+    and layer 2's projection reads it by DMA (k_mm); with
     SOMA_FLAG_FP32_SEQUENCE the sequence stays fp32 and the streaming
     projection splits it while staging.  Both split the same values the same
     way: losses and weights agree bit for bit."""
