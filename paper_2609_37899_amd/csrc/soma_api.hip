@@ -883,8 +883,13 @@ bool stream_weights(const soma_config& c) {
 
 template <bool kRad>
 // H > 128 (k_head_fused takes H <= 128), H % 64 == 0, H <= kStreamMaxH.
-void launch_head_stream_t(const soma::FwdArgs& a, int nslots, float2* hpart, float* htgt, hipStream_t st) {
-  const dim3 grid(unsigned(nslots * 2)), block(soma::kProjThreads);
+void launch_head_stream_t(const soma::FwdArgs& a, int nslots, int cus, float2* hpart, float* htgt, hipStream_t st) {
+  // A block forms its 128 rows of weights first (30 us at H = 512, Gaussian)
+  // and then takes 6 us for a 64-row tile: jobs are cut only where they leave
+  // compute units idle, into runs of at least eight tiles.
+  const int tiles = int((int64_t(a.T - 1) * a.B + 63) / 64);
+  const int split = std::max(1, std::min(cus / (2 * nslots), tiles / 8));
+  const dim3 grid(unsigned(nslots * 2), unsigned(split)), block(soma::kProjThreads);
   switch (a.H / 64) {
     case 3: hipLaunchKernelGGL((soma::k_head_stream<3, kRad>), grid, block, 0, st, a, nslots, hpart, htgt); break;
     case 4: hipLaunchKernelGGL((soma::k_head_stream<4, kRad>), grid, block, 0, st, a, nslots, hpart, htgt); break;
@@ -915,11 +920,11 @@ void launch_head_fused(const soma::FwdArgs& a, int nslots, hipStream_t st) {
     launch_head_fused_t<true>(a, nslots, st);
 }
 
-void launch_head_stream(const soma::FwdArgs& a, int nslots, float2* hpart, float* htgt, hipStream_t st) {
+void launch_head_stream(const soma::FwdArgs& a, int nslots, int cus, float2* hpart, float* htgt, hipStream_t st) {
   if (a.probe == SOMA_PROBE_GAUSSIAN)
-    launch_head_stream_t<false>(a, nslots, hpart, htgt, st);
+    launch_head_stream_t<false>(a, nslots, cus, hpart, htgt, st);
   else
-    launch_head_stream_t<true>(a, nslots, hpart, htgt, st);
+    launch_head_stream_t<true>(a, nslots, cus, hpart, htgt, st);
 }
 
 template <bool kRad>
@@ -1486,7 +1491,7 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
   } else if (kPert && stream_weights(c)) {
     float2* hpart = reinterpret_cast<float2*>(ctx->ws + L.hpart);
     float* htgt = reinterpret_cast<float*>(ctx->ws + L.htgt);
-    launch_head_stream(a, 2 * N * pcs, hpart, htgt, st);
+    launch_head_stream(a, 2 * N * pcs, ctx->cus, hpart, htgt, st);
     if (int rc = check_launch("k_head_stream")) return rc;
     hipLaunchKernelGGL(soma::k_ce_combine, dim3(L.row_tiles, 2 * N * pcs), dim3(64), 0, st, a, hpart, htgt);
     if (int rc = check_launch("k_ce_combine")) return rc;

@@ -1991,7 +1991,9 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_proj_stream(
 //   ce = M + ln(s_0 e^{m_0 - M} + s_1 e^{m_1 - M}) - logit_target,
 // M = max(m_0, m_1), and sums each 64-row tile in fp64 (the per-tile sums
 // that the loss reduction reads).
-// Partials: hpart[slot][half][R] float2 (m, s); htgt[slot][R].
+// Partials: hpart[slot][half][R] float2 (m, s); htgt[slot][R].  Where slots and
+// halves leave compute units idle (an evaluation has 2 N slots), grid.y > 1
+// blocks share a job, each with its own run of 64-row tiles.
 // ---------------------------------------------------------------------------
 // The library launches it for H > 128 (k_head_fused covers H <= 128); at
 // H <= 128 the probe scratch would be sized by K and the block would ask for
@@ -2049,7 +2051,10 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_head_stream(
   resident_weights_split<KC, false, kRad, ZW>(wh, wl, reinterpret_cast<float*>(lds), th, a.off_head, H, 0, H, vh * 128,
                                           a.probe, key, pair, step_lo, seps, a.err);
 
-  const int nchunks = ((R + 63) / 64) * NQ;
+  const int ntiles = (R + 63) / 64;             // this block's: tile0 .. tile1 - 1
+  const int tile0 = static_cast<int>(static_cast<int64_t>(ntiles) * blockIdx.y / gridDim.y);
+  const int tile1 = static_cast<int>(static_cast<int64_t>(ntiles) * (blockIdx.y + 1) / gridDim.y);
+  const int nchunks = tile1 * NQ;
   float4 pre[PT];
   auto gload = [&](int c) {
     const int r0 = (c / NQ) * 64, k0 = (c % NQ) * KW;
@@ -2084,12 +2089,12 @@ __global__ __launch_bounds__(kProjThreads, NCH <= 2 ? 4 : 1) void k_head_stream(
   // Row r0 + lr = ytt B + yb of the tile, advanced by 64 rows a tile; rows
   // 16 nb further on add the wave-uniform quotient and remainder of 16 nb
   // by B (rows past R read past the batch: 0 from the buffer, never stored).
-  int ytt = lr / B, yb = lr - (lr / B) * B;
+  int ytt = (tile0 * 64 + lr) / B, yb = tile0 * 64 + lr - ytt * B;
   const int q64 = 64 / B, r64 = 64 % B;
-  gload(0);
-  sstore(0);
+  gload(tile0 * NQ);
+  sstore((tile0 * NQ) & 1);
   __syncthreads();
-  for (int c = 0; c < nchunks; ++c) {
+  for (int c = tile0 * NQ; c < nchunks; ++c) {
     if (c + 1 < nchunks) gload(c + 1);
     const int buf = c & 1, qq = c % NQ, r0 = (c / NQ) * 64;
     if (qq == NQ - 1) {
