@@ -226,6 +226,24 @@ __device__ __forceinline__ float tanh_f(float x) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(__expf(2.0f * x) + 1.0f);
 }
 
+// Sum of logarithms of fp64 values in [2^-85, 2^101] (the rows' exponential
+// sums): eight factors are multiplied before a logarithm is taken, which costs
+// a hundred times a product and stood in every time step's serial chain.  The
+// product of eight stays within 2^+-808 and carries 8 x 2^-53.
+struct LogSum {
+  double sum = 0.0, prod = 1.0;
+  int n = 0;
+  __device__ __forceinline__ void add(double v) {
+    prod *= v;
+    if (++n == 8) {
+      sum += log(prod);
+      prod = 1.0;
+      n = 0;
+    }
+  }
+  __device__ __forceinline__ double total() const { return sum + log(prod); }
+};
+
 // Shape and workspace pointers shared by the forward kernels.
 struct FwdArgs {
   const float* theta;     // [N][d]
@@ -1647,6 +1665,7 @@ void k_rec_local(FwdArgs a, int jobs) {
   // partials (threads 0 .. B-1, one row each), merged, logged and the target
   // subtracted in fp64, summed per row in fp64.
   double cacc = 0.0;
+  LogSum clog;
   auto head_combine = [&](int par) {
     const int n = threadIdx.x;
     if (kHead && n < B) {
@@ -1666,7 +1685,8 @@ void k_rec_local(FwdArgs a, int jobs) {
 #pragma unroll
         for (int w = 0; w < 8; ++w) S += static_cast<double>(red[(par * 8 + w) * ROWS + n].y);
       }
-      cacc += (log(S) + static_cast<double>(M)) - static_cast<double>(tgl[par * ROWS + n]);
+      clog.add(S);
+      cacc += static_cast<double>(M) - static_cast<double>(tgl[par * ROWS + n]);
     }
   };
   // Cell updates of step t; h_t into buffer b (split) and to the slot's
@@ -1813,7 +1833,7 @@ void k_rec_local(FwdArgs a, int jobs) {
       head_partials(tl, (tl + 1) & 1);
       __syncthreads();
       head_combine((tl + 1) & 1);
-      if (threadIdx.x < ROWS) dsum[threadIdx.x] = cacc;
+      if (threadIdx.x < ROWS) dsum[threadIdx.x] = cacc + clog.total();
       __syncthreads();
       if (threadIdx.x == 0) {
         double tot = 0.0;
@@ -2297,7 +2317,8 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
   // by B (rows past R read past the batch: 0 from the buffer, never used).
   int ytt = lr / B, yb = lr - (lr / B) * B;
   const int q64 = 64 / B, r64 = 64 % B;
-  double cacc = 0.0;                          // this combining lane's ce sum (rows 16 wave + lane of every tile)
+  double cacc = 0.0;                          // this combining lane's ce sum (rows 16 wave + lane of every tile),
+  LogSum clog;                                // the logarithms apart
   f32x4 acc[4];
   // Rows of tile cc from the 16 waves' partials (waves 0..3, one per SIMD,
   // 16 rows each), summed, logged and the target subtracted in fp64: a loss
@@ -2321,7 +2342,8 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) S += static_cast<double>(red[cb][w][n].y);
       }
-      cacc += (log(S) + static_cast<double>(M)) - static_cast<double>(tgl[cb][n]);
+      clog.add(S);
+      cacc += static_cast<double>(M) - static_cast<double>(tgl[cb][n]);
     }
   };
   gload(0);
@@ -2396,7 +2418,7 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
   }
   combine(ntiles - 1);
   // The slot's total into its first tile partial, zeros in the others.
-  if (wave < 4 && lane < 16) dsum[wave * 16 + lane] = cacc;
+  if (wave < 4 && lane < 16) dsum[wave * 16 + lane] = cacc + clog.total();
   __syncthreads();
   double* part = a.part + slot * a.row_tiles;
   if (threadIdx.x == 0) {
