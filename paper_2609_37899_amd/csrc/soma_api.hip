@@ -19,7 +19,9 @@
 //                   fused into the recurrence)
 //   k_loss_reduce   fixed-order sums -> L_{e,j,+-} (fp64 means)
 // and then, once for the step:
-//   k_coef          c_{e,j} (independent) or dF_j / (2 eps_e P) (summed)
+//   k_coef          c_{e,j} (independent) or dF_j / (2 eps_e P) (summed); one
+//                   launch with the loss sums (k_loss_coef) where one chunk
+//                   holds every direction and the losses are independent
 //   k_update / k_update_adam   theta -= lr sum_j c_j z_j, regenerating z_j
 // The paper's width-32 body (SOMA_ARCH_BODY) runs its whole perturbed
 // forward in k_body (soma_body.hpp); the wide controls' body
@@ -433,36 +435,67 @@ __global__ void k_box_muller(const uint32_t* wa, const uint32_t* wb, float* za, 
   zb[i] = z.y;
 }
 
-// L[e][j0 + jl][s] = (sum over tiles in order) / (B (T-1)), accumulated in
-// fp64; the fp64 mean is kept (lossd) so that the antithetic difference is
-// taken before any rounding to fp32.  One thread per slot.
-__global__ void k_loss_reduce(const double* part, int row_tiles, int N, int pcs, int PC, int NS,
-                              int P, int j0, double inv_rows, float* losses, double* lossd,
-                              const unsigned* err) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * pcs * NS) return;
-  const int s = i % NS, jl = (i / NS) % pcs, e = i / (NS * pcs);
-  const double* p = part + ((int64_t(e) * PC + jl) * NS + s) * row_tiles;
+// The sum of n tile sums in fp64 by one wave: lane l adds l, l + 64, .. in
+// order, then the lanes meet in a fixed butterfly (every lane gets the same
+// value).  One thread a slot took 70 us for 255 tiles, a serial chain of loads.
+__device__ __forceinline__ double tile_sum(const double* p, int n) {
   double tot = 0.0;
-  for (int k = 0; k < row_tiles; ++k) tot += p[k];
-  if (err && *err) tot = __builtin_nan("");   // an aborted step (k_coef voids earlier chunks too)
-  const int64_t o = (int64_t(e) * P + j0 + jl) * NS + s;
-  losses[o] = static_cast<float>(tot * inv_rows);
-  if (lossd) lossd[o] = tot * inv_rows;
+  for (int k = threadIdx.x & 63; k < n; k += 64) tot += p[k];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) tot += __shfl_xor(tot, o);
+  return tot;
 }
 
-// loss[e] = (sum over tiles in order) / (B (T-1)) of slot (e, direction 0,
-// sign +) of a pass with PC directions per expert and both signs: the
-// evaluation that runs the step's kernels at radius 0.
-__global__ void k_eval_reduce(const double* part, int row_tiles, int N, int PC, double inv_rows, float* loss,
-                              const unsigned* err) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// L[e][j0 + jl][s] = (sum over tiles) / (B (T-1)), accumulated in fp64; the
+// fp64 mean is kept (lossd) so that the antithetic difference is taken before
+// any rounding to fp32.  One wave per slot, four a block.
+__global__ __launch_bounds__(256) void k_loss_reduce(const double* part, int row_tiles, int N, int pcs, int PC, int NS,
+                                                     int P, int j0, double inv_rows, float* losses, double* lossd,
+                                                     const unsigned* err) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= N * pcs * NS) return;
+  const int s = i % NS, jl = (i / NS) % pcs, e = i / (NS * pcs);
+  double tot = tile_sum(part + ((int64_t(e) * PC + jl) * NS + s) * row_tiles, row_tiles);
+  if (err && *err) tot = __builtin_nan("");   // an aborted step (k_coef voids earlier chunks too)
+  const int64_t o = (int64_t(e) * P + j0 + jl) * NS + s;
+  if ((threadIdx.x & 63) == 0) {
+    losses[o] = static_cast<float>(tot * inv_rows);
+    if (lossd) lossd[o] = tot * inv_rows;
+  }
+}
+
+// k_loss_reduce and k_coef in one launch, where one pass holds every direction
+// and each expert's coefficients come from its own losses: one wave per
+// (expert, direction), both signs.
+__global__ __launch_bounds__(256) void k_loss_coef(const double* part, int row_tiles, int N, int P, int PC,
+                                                   double inv_rows, const float* eps_v, int eps_stride, float* losses,
+                                                   double* lossd, float* coef, const unsigned* err) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (i >= N * P) return;
+  const int j = i % P, e = i / P;
+  const double* p = part + (int64_t(e) * PC + j) * 2 * row_tiles;
+  double lp = tile_sum(p, row_tiles) * inv_rows, lm = tile_sum(p + row_tiles, row_tiles) * inv_rows;
+  if (*err) lp = lm = __builtin_nan("");
+  if ((threadIdx.x & 63) == 0) {
+    losses[2 * int64_t(i)] = static_cast<float>(lp);
+    losses[2 * int64_t(i) + 1] = static_cast<float>(lm);
+    lossd[2 * int64_t(i)] = lp;
+    lossd[2 * int64_t(i) + 1] = lm;
+    const double inv_denom = 1.0 / (2.0 * double(eps_v[int64_t(e) * eps_stride]) * double(P));
+    coef[i] = static_cast<float>((lp - lm) * inv_denom);
+  }
+}
+
+// loss[e] = (sum over tiles) / (B (T-1)) of slot (e, direction 0, sign +) of a
+// pass with PC directions per expert and both signs: the evaluation that runs
+// the step's kernels at radius 0.  One wave per expert, four a block.
+__global__ __launch_bounds__(256) void k_eval_reduce(const double* part, int row_tiles, int N, int PC, double inv_rows,
+                                                     float* loss, const unsigned* err) {
+  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= N) return;
-  const double* p = part + (int64_t(e) * PC * 2) * row_tiles;
-  double tot = 0.0;
-  for (int k = 0; k < row_tiles; ++k) tot += p[k];
+  double tot = tile_sum(part + (int64_t(e) * PC * 2) * row_tiles, row_tiles);
   if (*err) tot = __builtin_nan("");
-  loss[e] = static_cast<float>(tot * inv_rows);
+  if ((threadIdx.x & 63) == 0) loss[e] = static_cast<float>(tot * inv_rows);
 }
 
 // c[e][j] = (L+ - L-) / (2 eps_e P) from the fp64 means, rounded once to fp32;
@@ -496,25 +529,30 @@ __global__ void k_coef(const double* lossd, int N, int P, int summed, const floa
   coef[i] = static_cast<float>(c);
 }
 
-// Per-expert rates of a step given as scalars: eps_v[e] = eps, lr_v[e] = lr.
-__global__ void k_fill_rates(float* eps_v, float* lr_v, int N, float eps, float lr) {
+// The start of a step given scalar rates (checked on the host): eps_v[e] = eps,
+// lr_v[e] = lr, and the abort flag cleared (err may be null).
+__global__ void k_begin(float* eps_v, float* lr_v, int N, float eps, float lr, unsigned* err) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e == 0 && err) *err = 0u;
   if (e < N) {
     eps_v[e] = eps;
     lr_v[e] = lr;
   }
 }
 
-// A step whose per-expert radius is not finite and > 0, or whose learning
-// rate is not finite, is aborted (the sticky flag; losses read NaN and the
-// parameters stay as they were).
-__global__ void k_check_rates(const float* eps_v, int eps_stride, const float* lr_v, int lr_stride, int N,
-                              unsigned* err) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= N) return;
-  const float eps = eps_v[int64_t(e) * eps_stride], lr = lr_v[int64_t(e) * lr_stride];
-  if (!(eps > 0.0f) || !__builtin_isfinite(eps) || !__builtin_isfinite(lr))
-    __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The start of a step with per-expert rates: a radius that is not finite and
+// > 0, or a learning rate that is not finite, aborts it (the sticky flag;
+// losses read NaN and the parameters stay as they were); else the flag is
+// cleared.  One block.
+__global__ __launch_bounds__(256) void k_begin_rates(const float* eps_v, int eps_stride, const float* lr_v,
+                                                     int lr_stride, int N, unsigned* err) {
+  int bad = 0;
+  for (int e = threadIdx.x; e < N; e += 256) {
+    const float eps = eps_v[int64_t(e) * eps_stride], lr = lr_v[int64_t(e) * lr_stride];
+    bad |= !(eps > 0.0f) || !__builtin_isfinite(eps) || !__builtin_isfinite(lr);
+  }
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) *err = bad ? 1u : 0u;
 }
 
 // The probe law of each coordinate: one law for the stacked LSTM; for the
@@ -1684,14 +1722,25 @@ struct Rates {
   int lr_stride;
 };
 
-// The scalar rates of a step, written to the workspace (no host copy).
+unsigned* abort_flag(const soma_ctx* ctx) { return reinterpret_cast<unsigned*>(ctx->ws + ctx->lay.sync) + kMaxGroups; }
+
+// The scalar rates of a step, written to the workspace (no host copy); clears
+// the abort flag.
 int scalar_rates(soma_ctx* ctx, float eps, float lr, hipStream_t st, Rates* out) {
   float* r = reinterpret_cast<float*>(ctx->ws + ctx->lay.rates);
   const int N = ctx->cfg.n_experts;
-  hipLaunchKernelGGL(soma::k_fill_rates, dim3((N + 255) / 256), dim3(256), 0, st, r, r + N, N, eps, lr);
-  if (int rc = check_launch("k_fill_rates")) return rc;
+  hipLaunchKernelGGL(soma::k_begin, dim3((N + 255) / 256), dim3(256), 0, st, r, r + N, N, eps, lr, abort_flag(ctx));
+  if (int rc = check_launch("k_begin")) return rc;
   *out = Rates{r, 1, r + N, 1};
   return SOMA_OK;
+}
+
+// The per-expert rates of a schedule, checked on the device; clears or sets
+// the abort flag.
+int checked_rates(soma_ctx* ctx, const Rates& r, hipStream_t st) {
+  hipLaunchKernelGGL(soma::k_begin_rates, dim3(1), dim3(256), 0, st, r.eps_v, r.eps_stride, r.lr_v, r.lr_stride,
+                     ctx->cfg.n_experts, abort_flag(ctx));
+  return check_launch("k_begin_rates");
 }
 
 Rates schedule_rates(const soma_schedule_entry* sched) {
@@ -1725,8 +1774,8 @@ int check_scalar_rates(float eps, float lr) {
 }
 
 // Steps 1-3 of the method: every perturbed forward, the losses and the
-// coefficients (in the workspace).  Returns the step's abort flag, which an
-// invalid per-expert rate sets.
+// coefficients (in the workspace).  The rates' launch (scalar_rates,
+// checked_rates) has put the abort flag in its first state.
 int forwards_and_coefficients(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t step,
                               const Rates& r, const uint8_t* bytes, float* losses, hipStream_t st,
                               unsigned** err_out) {
@@ -1736,34 +1785,35 @@ int forwards_and_coefficients(soma_ctx* ctx, const float* theta, const uint64_t*
   ctx->rec_launches = ctx->proj_launches = ctx->xchg_launches = 0;
   ctx->have_times = false;
   if (int rc = mark(ctx, kPhaseStart, st)) return rc;
-  unsigned* err = reinterpret_cast<unsigned*>(ctx->ws + L.sync) + kMaxGroups;
-  hipLaunchKernelGGL(soma::k_zero_u32, dim3(1), dim3(64), 0, st, err, 1);
-  if (int rc = check_launch("k_zero_u32")) return rc;
-  hipLaunchKernelGGL(soma::k_check_rates, dim3((c.n_experts + 255) / 256), dim3(256), 0, st, r.eps_v,
-                     r.eps_stride, r.lr_v, r.lr_stride, c.n_experts, err);
-  if (int rc = check_launch("k_check_rates")) return rc;
+  unsigned* err = abort_flag(ctx);
   const int D = dirs(c);
+  const double inv_rows = 1.0 / double(int64_t(c.seq_len - 1) * c.batch);
+  const double* part = reinterpret_cast<const double*>(ctx->ws + L.part);
+  double* lossd = reinterpret_cast<double*>(ctx->ws + L.lossd);
+  float* coef = reinterpret_cast<float*>(ctx->ws + L.coef);
+  const int nc = c.n_experts * D;
+  *err_out = err;
+  if (L.pc >= D && c.loss_mode != SOMA_LOSS_SUMMED) {
+    // One pass, each expert's coefficients from its own losses.
+    if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, 0, D, st)) return rc;
+    hipLaunchKernelGGL(soma::k_loss_coef, dim3((nc + 3) / 4), dim3(256), 0, st, part, L.row_tiles, c.n_experts, D, L.pc,
+                       inv_rows, r.eps_v, r.eps_stride, losses, lossd, coef, err);
+    if (int rc = check_launch("k_loss_coef")) return rc;
+    return mark(ctx, kPhaseReduce, st);
+  }
   for (int j0 = 0; j0 < D; j0 += L.pc) {
     const int pcs = std::min(L.pc, D - j0);
     if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, j0, pcs, st)) return rc;
     const int n = c.n_experts * pcs * 2;
-    const double inv_rows = 1.0 / double(int64_t(c.seq_len - 1) * c.batch);
-    hipLaunchKernelGGL(soma::k_loss_reduce, dim3((n + 255) / 256), dim3(256), 0, st,
-                       reinterpret_cast<const double*>(ctx->ws + L.part), L.row_tiles, c.n_experts,
-                       pcs, L.pc, 2, D, j0, inv_rows, losses,
-                       reinterpret_cast<double*>(ctx->ws + L.lossd), err);
+    hipLaunchKernelGGL(soma::k_loss_reduce, dim3((n + 3) / 4), dim3(256), 0, st, part, L.row_tiles, c.n_experts, pcs,
+                       L.pc, 2, D, j0, inv_rows, losses, lossd, err);
     if (int rc = check_launch("k_loss_reduce")) return rc;
     if (int rc = mark(ctx, kPhaseReduce, st)) return rc;
   }
-  float* coef = reinterpret_cast<float*>(ctx->ws + L.coef);
-  const int nc = c.n_experts * D;
-  hipLaunchKernelGGL(soma::k_coef, dim3((nc + 255) / 256), dim3(256), 0, st,
-                     reinterpret_cast<const double*>(ctx->ws + L.lossd), c.n_experts, D,
+  hipLaunchKernelGGL(soma::k_coef, dim3((nc + 255) / 256), dim3(256), 0, st, lossd, c.n_experts, D,
                      c.loss_mode == SOMA_LOSS_SUMMED ? 1 : 0, r.eps_v, r.eps_stride, coef, losses, err);
   if (int rc = check_launch("k_coef")) return rc;
-  if (int rc = mark(ctx, kPhaseReduce, st)) return rc;
-  *err_out = err;
-  return SOMA_OK;
+  return mark(ctx, kPhaseReduce, st);
 }
 
 // Adam hyperparameters checked and converted for update number t.
@@ -1886,8 +1936,9 @@ int soma_spsa_step_adam_sched(soma_ctx* ctx, float* theta, float* m, float* v, i
   if (!aligned(sched, alignof(soma_schedule_entry))) return fail(SOMA_EINVAL, "misaligned schedule");
   soma::AdamArgs h{};
   if (int rc = adam_args(hp, t, &h)) return rc;
-  return adam_step(ctx, theta, m, v, t, hp, seeds, step, schedule_rates(sched), bytes, losses,
-                   as_stream(stream));
+  const Rates r = schedule_rates(sched);
+  if (int rc = checked_rates(ctx, r, as_stream(stream))) return rc;
+  return adam_step(ctx, theta, m, v, t, hp, seeds, step, r, bytes, losses, as_stream(stream));
 }
 
 int soma_estimator_moments(soma_ctx* ctx, const uint64_t* seeds, uint64_t step, const float* coef, int32_t group,
@@ -1965,9 +2016,7 @@ int soma_eval_loss(soma_ctx* ctx, const float* theta, const uint8_t* bytes, floa
   ctx->timing = false;  // evaluation is not part of the step's phase record
   // The abort flag, set by a kernel that meets a weight outside the range of
   // its split products, makes the losses NaN.
-  unsigned* err = reinterpret_cast<unsigned*>(ctx->ws + L.sync) + kMaxGroups;
-  hipLaunchKernelGGL(soma::k_zero_u32, dim3(1), dim3(64), 0, st, err, 1);
-  if (int rc = check_launch("k_zero_u32")) return rc;
+  unsigned* err = abort_flag(ctx);
   const double inv_rows = 1.0 / double(int64_t(c.seq_len - 1) * c.batch);
   if (c.arch == SOMA_ARCH_LSTM && c.flags == 0) {
     // The step's kernels with radius 0: every weight is formed as
@@ -1975,23 +2024,24 @@ int soma_eval_loss(soma_ctx* ctx, const float* theta, const uint8_t* bytes, floa
     // unperturbed model (the probes are drawn and multiplied by zero; any
     // seeds do, so the fp64 loss area serves as their memory).  The + sign's
     // sum is the loss.
-    float* r = reinterpret_cast<float*>(ctx->ws + L.rates);
     const int N = c.n_experts;
-    hipLaunchKernelGGL(soma::k_fill_rates, dim3((N + 255) / 256), dim3(256), 0, st, r, r + N, N, 0.0f, 0.0f);
-    if (int rc = check_launch("k_fill_rates")) return rc;
+    Rates r{};
+    const int rcr = scalar_rates(ctx, 0.0f, 0.0f, st, &r);
     const uint64_t* any_seeds = reinterpret_cast<const uint64_t*>(ctx->ws + L.lossd);
-    const int rc0 = run_forward<true>(ctx, theta, any_seeds, 0, r, 1, bytes, 0, 1, st);
+    const int rc0 = rcr ? rcr : run_forward<true>(ctx, theta, any_seeds, 0, r.eps_v, 1, bytes, 0, 1, st);
     ctx->timing = timing;
     if (rc0) return rc0;
-    hipLaunchKernelGGL(soma::k_eval_reduce, dim3((N + 255) / 256), dim3(256), 0, st,
+    hipLaunchKernelGGL(soma::k_eval_reduce, dim3((N + 3) / 4), dim3(256), 0, st,
                        reinterpret_cast<const double*>(ctx->ws + L.part), L.row_tiles, N, L.pc, inv_rows, loss, err);
     if (int rc = check_launch("k_eval_reduce")) return rc;
     return ok();
   }
-  const int rc0 = run_forward<false>(ctx, theta, nullptr, 0, nullptr, 0, bytes, 0, 1, st);
+  hipLaunchKernelGGL(soma::k_zero_u32, dim3(1), dim3(64), 0, st, err, 1);
+  int rc0 = check_launch("k_zero_u32");
+  if (!rc0) rc0 = run_forward<false>(ctx, theta, nullptr, 0, nullptr, 0, bytes, 0, 1, st);
   ctx->timing = timing;
   if (rc0) return rc0;
-  hipLaunchKernelGGL(soma::k_loss_reduce, dim3((c.n_experts + 255) / 256), dim3(256), 0, st,
+  hipLaunchKernelGGL(soma::k_loss_reduce, dim3((c.n_experts + 3) / 4), dim3(256), 0, st,
                      reinterpret_cast<const double*>(ctx->ws + L.part), L.row_tiles, c.n_experts, 1,
                      1, 1, 1, 0, inv_rows, loss, static_cast<double*>(nullptr), err);
   if (int rc = check_launch("k_loss_reduce")) return rc;
@@ -2039,7 +2089,7 @@ int soma_head_delta(soma_ctx* ctx, const float* theta, const uint8_t* bytes, flo
   const double inv_rows = 1.0 / double(int64_t(c.seq_len - 1) * c.batch);
   const int width = c.arch == SOMA_ARCH_WIDE ? c.embed : c.hidden;
   if (loss) {
-    hipLaunchKernelGGL(soma::k_loss_reduce, dim3((c.n_experts + 255) / 256), dim3(256), 0, st,
+    hipLaunchKernelGGL(soma::k_loss_reduce, dim3((c.n_experts + 3) / 4), dim3(256), 0, st,
                        reinterpret_cast<const double*>(ctx->ws + L.part), L.row_tiles, c.n_experts, 1, 1, 1, 1, 0,
                        inv_rows, loss, static_cast<double*>(nullptr), err);
     if (int rc = check_launch("k_loss_reduce")) return rc;
