@@ -13,8 +13,10 @@
 //                   or k_rec_persist (one cooperative launch; blocks of a
 //                   group share the recurrent weights and stage h each step),
 //                   k_rec_local (H = 64: one block per perturbed model, h in
-//                   LDS, for L = 1 with the head and cross entropy fused), or
-//                   one launch per time step (k_rec_step_split / k_rec_step)
+//                   LDS, for L = 1 with the head and cross entropy fused),
+//                   k_rec_narrow (H an odd multiple of 16 up to 144: one block
+//                   per row tile, fp32 weights in registers), or one launch
+//                   per time step (k_rec_step_split / k_rec_step)
 //   k_head_stream + k_ce_combine   head and softmax cross entropy (unless
 //                   fused into the recurrence)
 //   k_loss_reduce   fixed-order sums -> L_{e,j,+-} (fp64 means)
@@ -48,6 +50,7 @@
 #include "soma_kernels.hpp"
 #include "soma_body.hpp"
 #include "soma_mm.hpp"
+#include "soma_narrow.hpp"
 #include "soma_wide.hpp"
 #include "soma_rec.hpp"
 
@@ -802,6 +805,40 @@ int launch_rec_split(const soma::FwdArgs& a, dim3 grid, hipStream_t st) {
   return SOMA_OK;
 }
 
+// Widths that are odd multiples of 16 up to kNarrowMaxH: the whole sequence in
+// one launch (k_rec_narrow), unless the launch per step is asked for.  Faster
+// at every batch and slot count tried: a step of 4 slots of 1 sequence (H = 144,
+// T = 200) 5.9 -> 1.6 ms, of 1024 slots of 128 (H = 80) 38.1 -> 26.2 ms.
+bool narrow_recurrence(const soma_config& c) {
+  return c.arch == SOMA_ARCH_LSTM && c.hidden % 32 == 16 && c.hidden <= soma::kNarrowMaxH &&
+         !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE);
+}
+
+template <int KG>
+int launch_narrow_t(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  // Two row tiles a block, which then share its weights and its barriers, only
+  // where one a block gives more blocks than compute units.
+  if (KG <= 7 && a.B > 16 && int64_t(slots) * ((a.B + 15) / 16) > cus) {
+    constexpr int K2 = KG <= 7 ? KG : 7;
+    hipLaunchKernelGGL((soma::k_rec_narrow<K2, 2>), dim3(unsigned(slots) * unsigned((a.B + 31) / 32)),
+                       dim3(64 * soma::narrow_waves(K2, 2)), 0, st, a, pert ? 1 : 0);
+  } else {
+    hipLaunchKernelGGL((soma::k_rec_narrow<KG, 1>), dim3(unsigned(slots) * unsigned((a.B + 15) / 16)),
+                       dim3(64 * soma::narrow_waves(KG, 1)), 0, st, a, pert ? 1 : 0);
+  }
+  return check_launch("k_rec_narrow");
+}
+
+int launch_narrow(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  switch (a.H / 16) {
+    case 1: return launch_narrow_t<1>(a, slots, cus, pert, st);
+    case 3: return launch_narrow_t<3>(a, slots, cus, pert, st);
+    case 5: return launch_narrow_t<5>(a, slots, cus, pert, st);
+    case 7: return launch_narrow_t<7>(a, slots, cus, pert, st);
+    default: return launch_narrow_t<9>(a, slots, cus, pert, st);   // H = 144 (narrow_recurrence)
+  }
+}
+
 int rec_row_block(int B) { return B <= 16 ? 16 : (B <= 32 ? 32 : 64); }
 
 // Groups of H / (4 NW) blocks that the persistent recurrence can run at once
@@ -1504,6 +1541,10 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       const int nw = soma::persist_waves(H, c.batch);
       const int blocks = groups * (H / (4 * nw));
       if (int rc = launch_persist(persist_kernel_for(c.batch, H, c.probe), p, blocks, 64 * nw, st)) return rc;
+      ctx->rec_launches += 1;
+    } else if (narrow_recurrence(c)) {
+      a.ns = kPert ? 2 : 1;
+      if (int rc = launch_narrow(a, a.ns * N * pcs, ctx->cus, kPert, st)) return rc;
       ctx->rec_launches += 1;
     } else {
       const dim3 grid((H / 16) * bgroups, pcs, N);

@@ -609,9 +609,8 @@ __global__ __launch_bounds__(kThreads) void k_rec_step(FwdArgs a) {
 // values of a chunk from two probe quads, splits both signs and runs the
 // three passes over the row tiles.  The fp32 products of k_rec_step share
 // the vector ALU's datapath with the probe generation; these run beside it.
-// Used where the shape rules out the persistent recurrence (H > 512 or
-// H % 64 != 0, B > 64) and H % 32 == 0; SOMA_FLAG_PER_STEP_RECURRENCE keeps
-// the fp32 k_rec_step.
+// Used where the shape rules out the persistent recurrences and H % 32 == 0;
+// SOMA_FLAG_PER_STEP_RECURRENCE keeps the fp32 k_rec_step.
 // ---------------------------------------------------------------------------
 constexpr int kStepSw = 32 + 16;   // staged row in halves (96 bytes: an odd multiple of 32)
 

@@ -1,0 +1,47 @@
+"""The one-launch recurrence of widths that are odd multiples of 16 (up to 144)
+against the launch per time step, which forms the same fp32 products and sums in
+the same order: the same losses, parameters and evaluation bit for bit, at every
+width it takes, batches around its row tiles, one step of recurrence and none,
+both block shapes (one and two row tiles), several chunks and a masked group."""
+import numpy as np
+import pytest
+
+from gpu_common import assert_losses_close, require_gpu
+from paper_2609_37899_amd import soma, synth
+
+pytestmark = pytest.mark.gpu
+
+
+# N, L, E, H, B, T, P, directions a pass, law, mask
+CASES = [(1, 1, 16, 16, 1, 2, 1, 0, 0, 0), (2, 2, 48, 16, 17, 9, 40, 0, 1, 0), (2, 2, 32, 48, 16, 3, 3, 2, 2, 0),
+         (3, 2, 48, 80, 10, 65, 4, 0, 2, 0), (4, 1, 64, 80, 33, 12, 32, 0, 0, soma.PERTURB_LSTM),
+         (1, 3, 112, 112, 31, 17, 5, 0, 1, 0), (4, 2, 16, 112, 70, 8, 30, 0, 0, 0),
+         (1, 2, 144, 144, 64, 6, 3, 0, 0, soma.PERTURB_HEAD), (2, 2, 32, 144, 5, 20, 2, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("N,L,E,H,B,T,P,pc,law,mask", CASES)
+def test_one_launch_is_the_launch_per_step(oracle_mod, N, L, E, H, B, T, P, pc, law, mask):
+    torch = require_gpu()
+    theta = synth.init_theta(N, L, E, H, init_seed=4, distinct=True)
+    data = synth.expert_batches([70 + e for e in range(N)], B, T)
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    outs, launches = [], []
+    for flags in (0, soma.FLAG_PER_STEP_RECURRENCE):
+        ctx = soma.Context(soma.Shape(N, L, E, H, B, T, P, 0, pc, flags, law, 1, soma.ARCH_LSTM, mask))
+        ctx.set_phase_timing(True)
+        th, db = torch.from_numpy(theta.copy()).cuda(), torch.from_numpy(data).cuda()
+        losses = torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+        print(f"H={H} B={B} T={T} flags={flags}: evaluation, step", flush=True)
+        ctx.eval_loss(th, db, loss)
+        ctx.spsa_step(th, seeds, 2, 1e-3, 1e-2, db, losses)
+        launches.append(ctx.phase_times()["rec_launches"])
+        torch.cuda.synchronize()
+        outs.append([x.cpu().numpy() for x in (th, losses, loss)])
+        ctx.close()
+    chunks = (P + (pc or P) - 1) // (pc or P)
+    assert launches == [L * chunks, L * (T - 1) * chunks]
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+    cfg = oracle_mod.make_cfg(N, L, E, H, B, T, P)
+    assert_losses_close(outs[0][2], oracle_mod.eval_loss(cfg, theta, data))
