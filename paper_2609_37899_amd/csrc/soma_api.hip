@@ -839,6 +839,83 @@ int launch_narrow(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStre
   }
 }
 
+// The projection and the head with their weights drawn once (k_proj_narrow,
+// k_head_narrow): widths that are no multiple of 64, up to kNarrowMaxH, unless
+// the kernels that draw them per row tile are asked for.
+bool narrow_weights(const soma_config& c) {
+  return c.arch == SOMA_ARCH_LSTM && c.hidden % 64 != 0 && c.hidden <= soma::kNarrowMaxH &&
+         !(c.flags & SOMA_FLAG_TILED_WEIGHTS);
+}
+
+// How many blocks share a slot's row tiles, and what the launch then takes, in
+// tiles: whole rounds of the `resident` blocks that the chip holds, each as
+// long as a block's tiles and the forming of its weights (about one tile).
+struct NarrowSplit {
+  unsigned split;
+  double cost;
+};
+
+NarrowSplit narrow_split(int64_t blocks, int tiles, int64_t resident) {
+  NarrowSplit best{1, 1e300};
+  for (int64_t s = 1; s <= std::min(tiles, 64); ++s) {
+    const double cost = double((blocks * s + resident - 1) / resident) * double((tiles + s - 1) / s + 1);
+    if (cost < best.cost) best = NarrowSplit{unsigned(s), cost};
+  }
+  return best;
+}
+
+// The projection takes it where that is within 1.5 times of its tiles over a
+// full chip: k_proj, which draws the probes again per 128 rows but for both signs
+// at once, takes 1.65 to 1.85 times at every slot count (H = 80, 10 tiles a slot:
+// 128 slots 69 against 96 us, cost 1.2; 48 slots, cost 1.6: 52 against 46).  The
+// head takes it always (k_head_ce: 2.1 times; 129 slots at H = 144 441 against
+// 432 us with the rounds at their worst and no split).
+bool narrow_projection(const soma_config& c, int slots, int row_tiles, int cus) {
+  if (!narrow_weights(c)) return false;
+  const int64_t blocks = int64_t(slots) * soma::narrow_proj_blocks(c.hidden / 16);
+  return narrow_split(blocks, row_tiles, 2 * cus).cost * 2 * cus <= 1.5 * double(blocks) * row_tiles;
+}
+
+template <int KG>
+void launch_proj_narrow_t(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  const unsigned blocks = unsigned(slots) * soma::narrow_proj_blocks(KG);
+  hipLaunchKernelGGL((soma::k_proj_narrow<KG>), dim3(blocks, narrow_split(blocks, a.row_tiles, 2 * cus).split),
+                     dim3(soma::kThreads), 0, st, a, pert ? 1 : 0, a.row_tiles);
+}
+
+template <int KG>
+void launch_head_narrow_t(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  const unsigned split = narrow_split(slots, a.row_tiles, soma::narrow_head_blocks(KG) * cus).split;
+  hipLaunchKernelGGL((soma::k_head_narrow<KG>), dim3(unsigned(slots), split),
+                     dim3(soma::kThreads), 0, st, a, pert ? 1 : 0);
+}
+
+int launch_proj_narrow(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  switch (a.H / 16) {
+    case 1: launch_proj_narrow_t<1>(a, slots, cus, pert, st); break;
+    case 2: launch_proj_narrow_t<2>(a, slots, cus, pert, st); break;
+    case 3: launch_proj_narrow_t<3>(a, slots, cus, pert, st); break;
+    case 5: launch_proj_narrow_t<5>(a, slots, cus, pert, st); break;
+    case 6: launch_proj_narrow_t<6>(a, slots, cus, pert, st); break;
+    case 7: launch_proj_narrow_t<7>(a, slots, cus, pert, st); break;
+    default: launch_proj_narrow_t<9>(a, slots, cus, pert, st); break;   // H = 144 (narrow_weights)
+  }
+  return check_launch("k_proj_narrow");
+}
+
+int launch_head_narrow(const soma::FwdArgs& a, int slots, int cus, bool pert, hipStream_t st) {
+  switch (a.H / 16) {
+    case 1: launch_head_narrow_t<1>(a, slots, cus, pert, st); break;
+    case 2: launch_head_narrow_t<2>(a, slots, cus, pert, st); break;
+    case 3: launch_head_narrow_t<3>(a, slots, cus, pert, st); break;
+    case 5: launch_head_narrow_t<5>(a, slots, cus, pert, st); break;
+    case 6: launch_head_narrow_t<6>(a, slots, cus, pert, st); break;
+    case 7: launch_head_narrow_t<7>(a, slots, cus, pert, st); break;
+    default: launch_head_narrow_t<9>(a, slots, cus, pert, st); break;   // H = 144 (narrow_weights)
+  }
+  return check_launch("k_head_narrow");
+}
+
 int rec_row_block(int B) { return B <= 16 ? 16 : (B <= 32 ? 32 : 64); }
 
 // Groups of H / (4 NW) blocks that the persistent recurrence can run at once
@@ -1504,6 +1581,9 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       } else if (kPert && stream_weights(c)) {
         launch_proj_stream(a, 2 * N * pcs, st);
         if (int rc = check_launch("k_proj_stream")) return rc;
+      } else if (narrow_projection(c, (kPert ? 2 : 1) * N * pcs, L.row_tiles, ctx->cus)) {
+        a.ns = kPert ? 2 : 1;
+        if (int rc = launch_proj_narrow(a, a.ns * N * pcs, ctx->cus, kPert, st)) return rc;
       } else {
         hipLaunchKernelGGL((soma::k_proj<kPert>),
                            dim3(4 * H / 64, unsigned((R + 127) / 128), N * pcs),
@@ -1574,6 +1654,9 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
     if (int rc = check_launch("k_head_stream")) return rc;
     hipLaunchKernelGGL(soma::k_ce_combine, dim3(L.row_tiles, 2 * N * pcs), dim3(64), 0, st, a, hpart, htgt);
     if (int rc = check_launch("k_ce_combine")) return rc;
+  } else if (narrow_weights(c)) {
+    a.ns = kPert ? 2 : 1;
+    if (int rc = launch_head_narrow(a, a.ns * N * pcs, ctx->cus, kPert, st)) return rc;
   } else {
     hipLaunchKernelGGL((soma::k_head_ce<kPert>), dim3(L.row_tiles, N * pcs), dim3(soma::kThreads), 0,
                        st, a);

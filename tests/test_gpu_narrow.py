@@ -45,3 +45,33 @@ def test_one_launch_is_the_launch_per_step(oracle_mod, N, L, E, H, B, T, P, pc, 
         assert np.isfinite(a).all() and np.array_equal(a, b)
     cfg = oracle_mod.make_cfg(N, L, E, H, B, T, P)
     assert_losses_close(outs[0][2], oracle_mod.eval_loss(cfg, theta, data))
+
+
+# the widths of the resident projection and head; few and many slots (rows of a
+# slot cut into runs that end in a ragged tile, or whole), B beyond 16 and below
+@pytest.mark.parametrize("N,L,E,H,B,T,P,pc,law,mask",
+                         [(1, 1, 16, 16, 3, 9, 1, 0, 0, 0), (8, 2, 16, 16, 40, 30, 32, 0, 0, 0),
+                          (2, 2, 32, 32, 17, 40, 64, 0, 1, 0), (4, 2, 48, 48, 65, 9, 40, 7, 2, 0),
+                          (2, 2, 48, 80, 10, 65, 40, 0, 0, soma.PERTURB_HEAD), (3, 1, 96, 96, 1, 300, 50, 0, 0, 0),
+                          (4, 2, 96, 96, 33, 20, 40, 0, 2, 0), (3, 2, 112, 112, 5, 70, 43, 0, 0, soma.PERTURB_LSTM),
+                          (2, 2, 144, 144, 64, 12, 48, 0, 1, 0), (1, 3, 144, 144, 2, 33, 129, 0, 0, 0)])
+def test_resident_weights_are_the_tiled_weights(N, L, E, H, B, T, P, pc, law, mask):
+    """k_proj_narrow and k_head_narrow against k_proj and k_head_ce: the same bits."""
+    torch = require_gpu()
+    theta = synth.init_theta(N, L, E, H, init_seed=4, distinct=True)
+    data = synth.expert_batches([70 + e for e in range(N)], B, T)
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    outs = []
+    for flags in (0, soma.FLAG_TILED_WEIGHTS):
+        ctx = soma.Context(soma.Shape(N, L, E, H, B, T, P, 0, pc, flags, law, 1, soma.ARCH_LSTM, mask))
+        th, db = torch.from_numpy(theta.copy()).cuda(), torch.from_numpy(data).cuda()
+        losses = torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+        print(f"H={H} B={B} T={T} flags={flags}: evaluation, step", flush=True)
+        ctx.eval_loss(th, db, loss)
+        ctx.spsa_step(th, seeds, 2, 1e-3, 1e-2, db, losses)
+        torch.cuda.synchronize()
+        outs.append([x.cpu().numpy() for x in (th, losses, loss)])
+        ctx.close()
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
