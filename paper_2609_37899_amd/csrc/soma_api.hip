@@ -1224,9 +1224,15 @@ int launch_mm_t(soma::MmArgs m, int slots, int cus, hipStream_t st) {
 // down projection at d_p = 384); 128 x 128 else.  At the wide control's sizes
 // (64 slots, 65,472 rows, K = 384) against 128 x 128 throughout: gates (N =
 // 1,536) 13.0 against 16.0 ms, GELU 15.1 against 16.8, down projection (N = 384,
-// K = 1,536) 13.5 against 14.6.
+// K = 1,536) 13.5 against 14.6.  128 x 128 also where the chip holds all of those
+// tiles at once (two blocks a compute unit): a large tile would leave units idle
+// and take four times as long for one that is mostly padding.  Whole steps: wide
+// control of 8 slots of 16 rows 618 -> 467 us, of 8 slots of 2,048 rows 1,179 ->
+// 1,113; stacked LSTM, 8 slots of 64 rows, H = 512, 258 -> 237.
 template <int kEpi>
 int launch_mm(soma::MmArgs m, int slots, int cus, hipStream_t st) {
+  const int64_t small = int64_t((m.N + 127) / 128) * ((m.M + 127) / 128) * slots;
+  if (small <= 2 * cus) return launch_mm_t<kEpi, 8, 8, 2, 2>(m, slots, cus, st);
   if (m.N % 256 == 0) return launch_mm_t<kEpi, 16, 16, 2, 4>(m, slots, cus, st);
   if (m.N % 384 == 0) return launch_mm_t<kEpi, 24, 8, 4, 2>(m, slots, cus, st);
   return launch_mm_t<kEpi, 8, 8, 2, 2>(m, slots, cus, st);

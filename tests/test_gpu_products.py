@@ -17,8 +17,18 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("H,B,T", [(128, 33, 2), (192, 64, 5), (320, 48, 7), (256, 100, 4)])
 def test_projection_equals_the_streaming_one(H, B, T):
+    check_projection(H, B, T, 2)
+
+
+# More 128 x 128 tiles than the chip holds at once: the large tiles run.
+@pytest.mark.parametrize("H,B,T", [(128, 33, 7), (192, 64, 5), (256, 100, 5)])
+def test_projection_on_large_tiles_equals_the_streaming_one(H, B, T):
+    check_projection(H, B, T, 80)
+
+
+def check_projection(H, B, T, P):
     torch = require_gpu()
-    N, L, E, P = 1, 3, 32, 2
+    N, L, E = 1, 3, 32
     theta = torch.from_numpy(synth.init_theta(N, L, E, H, init_seed=5)).cuda()
     data = torch.from_numpy(synth.expert_batches([900], B, T)).cuda()
     seeds = soma.seeds_tensor(synth.expert_seeds(N))
@@ -37,8 +47,17 @@ def test_projection_equals_the_streaming_one(H, B, T):
 
 @pytest.mark.parametrize("dt,B,T", [(50, 7, 3), (190, 16, 9), (250, 17, 9), (361, 43, 4), (300, 64, 5), (449, 34, 9)])
 def test_wide_products_match_oracle(oracle_mod, dt, B, T):
+    check_wide(oracle_mod, dt, B, T, 2)
+
+
+@pytest.mark.parametrize("dt,B,T", [(250, 17, 9), (361, 43, 4), (449, 34, 9)])
+def test_wide_products_on_large_tiles_match_oracle(oracle_mod, dt, B, T):
+    check_wide(oracle_mod, dt, B, T, 40)
+
+
+def check_wide(oracle_mod, dt, B, T, P):
     torch = require_gpu()
-    N, D, P = 2, 1, 2
+    N, D = 2, 1
     theta = synth.init_wide(N, D, dt, 32, init_seed=7, distinct=True)
     head = synth.init_tied_head(32, init_seed=8, n_experts=N)
     data = synth.expert_batches([950 + e for e in range(N)], B, T)
