@@ -255,12 +255,16 @@ int64_t tile_rows(const soma_config& c) { return int64_t(c.seq_len - 1) * ((c.ba
 // as well (H = 128, B = 33, 128 jobs of 99 steps: 0.81 against 0.98 ms a
 // layer) -- at every width its registers hold: H a multiple of 64 up to 704 (up to 512 on the wide body's pre-formed weights;
 // the stacked LSTM at H = 64 has k_rec_local).  Batches beyond 64 are cut into
-// jobs of 64.  It addresses a slot's gate inputs with 32-bit offsets.  Whether
+// jobs of 64, from four time steps on: below that the launch per step is ahead
+// (eight slots of 100 sequences, two layers, H = 128: one step 75 against
+// 134 us, eight 361 against 210; H = 704: 211 against 443, 1,314 against 829).
+// It addresses a slot's gate inputs with 32-bit offsets.  Whether
 // it runs also depends on the device (compute units per XCD).
 bool xchg_shape(const soma_config& c) {
   const int H = rec_width(c);
   if (c.arch == SOMA_ARCH_BODY || H % 64 != 0 || H > (c.arch == SOMA_ARCH_WIDE ? 512 : soma::kRecMaxH)) return false;
   if (c.arch == SOMA_ARCH_LSTM && H < 128) return false;
+  if (c.batch > 64 && c.seq_len < 5) return false;
   const int64_t gin_slot_bytes = tile_rows(c) * 4 * H * int64_t(sizeof(float));
   return c.batch > 32 && gin_slot_bytes < (int64_t(1) << 31) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
          !(c.flags & SOMA_FLAG_STAGED_RECURRENCE);

@@ -28,7 +28,7 @@ CASES = [
     (1, 2, 48, 448, 48, 4, 2, 0),     # three whole tiles
     (1, 2, 32, 576, 49, 4, 1, 2),
     (1, 2, 32, 640, 64, 3, 1, 0),
-    (1, 1, 32, 384, 129, 2, 1, 0),    # three jobs of one step
+    (1, 1, 32, 384, 129, 5, 1, 0),    # three jobs, the fewest steps of a batch cut into jobs
 ]
 
 
