@@ -269,10 +269,10 @@ int soma_spsa_step(soma_ctx* ctx, float* theta_dev, const uint64_t* seeds_dev, u
 /* soma_spsa_step for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * no context and no workspace.  The step's scratch space is a static device
- * array of the library, 32 MiB on each GPU it runs on (and 24 MiB more for the
- * exchange recurrence, which shapes are not held to), held until the process
- * ends; shapes whose workspace for one direction at a time exceeds the 32 MiB
- * return SOMA_ESHAPE (the tiny and small shapes fit: the N = 1, H = 64
+ * array of the library, 32 MiB on each GPU it runs on (and 24 MiB more for what
+ * the exchange recurrence adds, at no width or batch counted against a shape),
+ * held until the process ends; shapes whose workspace for one direction at a
+ * time exceeds the 32 MiB return SOMA_ESHAPE (the tiny and small shapes fit: the N = 1, H = 64
  * workload needs 1.3 MB).  The directions run in the largest chunk that fits
  * (or cfg->pair_chunk).  Stacked LSTM only (SOMA_EINVAL for SOMA_ARCH_BODY).
  * Calls share that array on each GPU: calls that overlap on one GPU (two

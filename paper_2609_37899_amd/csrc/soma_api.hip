@@ -2365,24 +2365,28 @@ int scratch_address(char** out) {
   return SOMA_OK;
 }
 
-// The largest direction chunk whose workspace fits `budget` bytes (the
-// configured chunk if one is set), or 0 if none does.  The limit holds shapes
-// to what they need on the staged recurrence; the exchange's area lies beyond
-// it, except for the batches and widths that have always counted it.
-size_t scratch_need(const soma_config& c, int pc) {
-  const Layout L = layout_for(c, pc, false);
-  const int H = c.hidden;
+// What counts against the limit: the layout of the staged recurrence.  The
+// exchange's ring and the padding of its gate inputs to whole row tiles lie in
+// the bytes beyond it, at every width and batch.
+size_t scratch_need(const soma_config& c, const Layout& L) {
   if (L.xch_bytes == 0) return L.total;
-  const bool counted = c.batch > 48 && c.batch <= 64 && (H == 128 || H == 256 || H == 512 || H == 704);
-  const size_t per_row = c.n_layers > 1 ? sizeof(float) * c.n_experts * size_t(pc) * 2 * 4 * H : 0;
+  const size_t per_row = c.n_layers > 1 ? sizeof(float) * c.n_experts * size_t(L.pc) * 2 * 4 * c.hidden : 0;
   const size_t padding = round_up(per_row * tile_rows(c)) - round_up(per_row * (c.seq_len - 1) * c.batch);
-  return (counted ? L.total : L.xch) - padding;   // the area ends the layout
+  return L.xch - padding;   // the exchange's area ends the layout
 }
 
-int chunk_within(const soma_config& c, size_t budget) {
-  if (c.pair_chunk > 0) return scratch_need(c, c.pair_chunk) <= budget ? c.pair_chunk : 0;
+// Whether the step fits the array in chunks of pc directions.
+bool fits_scratch(const soma_config& c, int pc) {
+  const Layout L = layout_for(c, pc, false);
+  return scratch_need(c, L) <= kStaticScratchBytes && L.total <= kStaticScratchBytes + kExchangeScratchBytes;
+}
+
+// The largest direction chunk that fits (the configured chunk if one is set),
+// or 0 if none does.
+int static_chunk(const soma_config& c) {
+  if (c.pair_chunk > 0) return fits_scratch(c, c.pair_chunk) ? c.pair_chunk : 0;
   for (int pc = dirs(c); pc >= 1; --pc)
-    if (scratch_need(c, pc) <= budget) return pc;
+    if (fits_scratch(c, pc)) return pc;
   return 0;
 }
 
@@ -2392,10 +2396,12 @@ extern "C" int soma_spsa_step_noalloc(const soma_config* cfg, float* theta, cons
                                       float eps, float lr, const uint8_t* bytes, float* losses, void* stream) {
   if (int rc = validate(cfg)) return rc;
   if (cfg->arch != SOMA_ARCH_LSTM) return fail(SOMA_EINVAL, "soma_spsa_step_noalloc runs the stacked LSTM only");
-  const int pc = chunk_within(*cfg, kStaticScratchBytes);
-  if (pc == 0)
-    return fail(SOMA_ESHAPE, "this shape needs %zu bytes of scratch per direction; the static scratch holds %zu",
-                scratch_need(*cfg, 1), kStaticScratchBytes);
+  const int pc = static_chunk(*cfg);
+  if (pc == 0) {
+    const int least = cfg->pair_chunk > 0 ? cfg->pair_chunk : 1;
+    return fail(SOMA_ESHAPE, "this shape needs %zu bytes of scratch for %d direction(s) at a time; the static scratch holds %zu",
+                scratch_need(*cfg, layout_for(*cfg, least, false)), least, kStaticScratchBytes);
+  }
   char* ws = nullptr;
   if (int rc = scratch_address(&ws)) return rc;
   const Layout L = layout_for(*cfg, pc, false);

@@ -162,3 +162,16 @@ def test_wide_body_parameter_counts_and_chunks(lib):
     ws = soma.workspace_size(shape_of(w))
     assert ws <= 64 * 2**30
     assert ws == soma.workspace_size(shape_of(w, pair_chunk=16))
+
+
+@pytest.mark.parametrize("H,B,T,fits", [
+    (256, 64, 200, True), (256, 48, 260, True), (320, 64, 160, True), (512, 64, 96, True), (128, 100, 250, True),
+    (256, 64, 240, False), (320, 64, 200, False)])
+def test_static_scratch_holds_every_width_to_the_same_limit(lib, H, B, T, fits):
+    """The step without a workspace counts what a shape needs on the staged recurrence against its
+    32 MiB, at every width and batch; what the exchange recurrence adds lies beyond.  (No pointers:
+    a shape that fits gets as far as the device, or the check of its pointers, and no launch.)"""
+    cfg = soma.Shape(1, 1, 32, H, B, T, 1).cfg()
+    rc = lib.soma_spsa_step_noalloc(ctypes.byref(cfg), None, None, 0, 1e-3, 1e-3, None, None, None)
+    assert (rc == soma.SOMA_ESHAPE) == (not fits), lib.soma_last_error()
+    assert rc in (soma.SOMA_ESHAPE, soma.SOMA_EDEVICE, soma.SOMA_EINVAL)
