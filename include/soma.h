@@ -496,6 +496,12 @@ int soma_set_spin_limit(soma_ctx* ctx, uint32_t polls);
  * Returns SOMA_EINVAL if no step ran with timing enabled. */
 int soma_get_phase_times(soma_ctx* ctx, soma_phase_times* out);
 
+/* How many input projections of ctx's last step, and of the evaluations since
+ * it, ran with a slot's weights held in registers at a width that is no
+ * multiple of 64 (k_proj_narrow; the rule goes by slots and rows, so that a
+ * test has to ask).  Errors: SOMA_EINVAL for a NULL argument. */
+int soma_get_narrow_projections(const soma_ctx* ctx, int32_t* launches);
+
 /* Thread-local description of the last error ("" if none). */
 const char* soma_last_error(void);
 

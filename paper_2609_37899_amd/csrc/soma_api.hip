@@ -389,7 +389,7 @@ struct soma_ctx {
   std::vector<hipEvent_t> events;   // pool, grows on demand
   std::vector<int> phase;           // phase closed by events[i]
   size_t nmarks;
-  int rec_launches, proj_launches, xchg_launches;
+  int rec_launches, proj_launches, xchg_launches, narrow_projections;
 };
 
 namespace soma {
@@ -1594,6 +1594,7 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
       } else if (narrow_projection(c, (kPert ? 2 : 1) * N * pcs, L.row_tiles, ctx->cus)) {
         a.ns = kPert ? 2 : 1;
         if (int rc = launch_proj_narrow(a, a.ns * N * pcs, ctx->cus, kPert, st)) return rc;
+        ++ctx->narrow_projections;
       } else {
         hipLaunchKernelGGL((soma::k_proj<kPert>),
                            dim3(4 * H / 64, unsigned((R + 127) / 128), N * pcs),
@@ -1762,7 +1763,7 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
   ctx->spin_limit = kSpinLimit;
   ctx->have_times = false;
   ctx->nmarks = 0;
-  ctx->rec_launches = ctx->proj_launches = ctx->xchg_launches = 0;
+  ctx->rec_launches = ctx->proj_launches = ctx->xchg_launches = ctx->narrow_projections = 0;
 }
 
 }  // namespace
@@ -1843,6 +1844,12 @@ int soma_get_phase_times(soma_ctx* ctx, soma_phase_times* out) {
   return ok();
 }
 
+int soma_get_narrow_projections(const soma_ctx* ctx, int32_t* launches) {
+  if (!ctx || !launches) return fail(SOMA_EINVAL, "NULL argument");
+  *launches = ctx->narrow_projections;
+  return ok();
+}
+
 }  // extern "C"
 
 namespace {
@@ -1916,7 +1923,7 @@ int forwards_and_coefficients(soma_ctx* ctx, const float* theta, const uint64_t*
   const soma_config& c = ctx->cfg;
   const Layout& L = ctx->lay;
   ctx->nmarks = 0;
-  ctx->rec_launches = ctx->proj_launches = ctx->xchg_launches = 0;
+  ctx->rec_launches = ctx->proj_launches = ctx->xchg_launches = ctx->narrow_projections = 0;
   ctx->have_times = false;
   if (int rc = mark(ctx, kPhaseStart, st)) return rc;
   unsigned* err = abort_flag(ctx);

@@ -28,7 +28,7 @@ EXPORTS = ("soma_param_count", "soma_workspace_size", "soma_create", "soma_destr
            "soma_apply_update", "soma_apply_adam", "soma_spsa_step_adam_sched", "soma_schedule_init",
            "soma_schedule_observe", "soma_estimator_moments", "soma_set_tied_head", "soma_head_delta",
            "soma_gaussian", "soma_probe", "soma_philox", "soma_box_muller", "soma_set_phase_timing",
-           "soma_get_phase_times", "soma_set_spin_limit", "soma_spsa_step_noalloc",
+           "soma_get_phase_times", "soma_get_narrow_projections", "soma_set_spin_limit", "soma_spsa_step_noalloc",
            "soma_last_error")
 
 
@@ -118,6 +118,7 @@ def load():
             "soma_set_phase_timing": (ctypes.c_int, [vp, ctypes.c_int]),
             "soma_set_spin_limit": (ctypes.c_int, [vp, ctypes.c_uint32]),
             "soma_get_phase_times": (ctypes.c_int, [vp, ctypes.POINTER(PhaseTimes)]),
+            "soma_get_narrow_projections": (ctypes.c_int, [vp, ctypes.POINTER(ctypes.c_int32)]),
             "soma_last_error": (ctypes.c_char_p, []),
         }
         for name, (res, args) in sig.items():
@@ -263,6 +264,11 @@ class Context:
     def set_spin_limit(self, polls: int):
         """Polls per group barrier of the persistent recurrence (0: default)."""
         _check(load().soma_set_spin_limit(self._h, int(polls)))
+
+    def narrow_projections(self) -> int:
+        out = ctypes.c_int32()
+        _check(load().soma_get_narrow_projections(self._h, ctypes.byref(out)))
+        return out.value
 
     def phase_times(self) -> dict:
         out = PhaseTimes()

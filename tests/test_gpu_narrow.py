@@ -56,7 +56,8 @@ def test_one_launch_is_the_launch_per_step(oracle_mod, N, L, E, H, B, T, P, pc, 
                           (4, 2, 96, 96, 33, 20, 40, 0, 2, 0), (3, 2, 112, 112, 5, 70, 43, 0, 0, soma.PERTURB_LSTM),
                           (2, 2, 144, 144, 64, 12, 48, 0, 1, 0), (1, 3, 144, 144, 2, 33, 129, 0, 0, 0)])
 def test_resident_weights_are_the_tiled_weights(N, L, E, H, B, T, P, pc, law, mask):
-    """k_proj_narrow and k_head_narrow against k_proj and k_head_ce: the same bits."""
+    """k_head_narrow, and k_proj_narrow where its slots fill the chip (the test below sees to
+    that), against k_head_ce and k_proj: the same bits."""
     torch = require_gpu()
     theta = synth.init_theta(N, L, E, H, init_seed=4, distinct=True)
     data = synth.expert_batches([70 + e for e in range(N)], B, T)
@@ -75,3 +76,65 @@ def test_resident_weights_are_the_tiled_weights(N, L, E, H, B, T, P, pc, law, ma
         ctx.close()
     for a, b in zip(*outs):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+# Slots and 64-row tiles at which the resident projection runs on 256 compute
+# units, at every width it has an instance for: rows of a slot in one, two, three
+# and four runs, ragged last tiles, gate tiles dealt evenly over a slot's blocks
+# and not (H = 80: 20 over 2 x 4 waves, 112: 28 over 4 x 4, 144: 36 over 3 x 4).
+PROJ_CASES = [(1, 2, 16, 16, 64, 9, 64, 0, 0, 0), (4, 3, 32, 32, 5, 20, 64, 0, 1, 0), (2, 2, 48, 48, 18, 31, 40, 0, 2, 0),
+              (4, 2, 16, 48, 13, 8, 64, 0, 0, soma.PERTURB_LSTM), (2, 2, 80, 80, 33, 16, 32, 0, 0, 0),
+              (4, 3, 32, 80, 17, 10, 64, 32, 2, 0), (1, 2, 48, 96, 7, 72, 32, 0, 1, 0),
+              (1, 2, 112, 112, 20, 23, 32, 0, 0, 0), (2, 2, 16, 112, 50, 3, 32, 0, 1, soma.PERTURB_HEAD),
+              (2, 2, 144, 144, 31, 17, 32, 0, 0, 0), (4, 2, 32, 144, 21, 22, 32, 0, 2, 0)]
+
+
+@pytest.mark.parametrize("N,L,E,H,B,T,P,pc,law,mask", PROJ_CASES)
+def test_resident_projection_is_the_tiled_one(N, L, E, H, B, T, P, pc, law, mask):
+    torch = require_gpu()
+    theta = synth.init_theta(N, L, E, H, init_seed=6, distinct=True)
+    data = synth.expert_batches([90 + e for e in range(N)], B, T)
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    outs, launches = [], []
+    for flags in (0, soma.FLAG_TILED_WEIGHTS):
+        ctx = soma.Context(soma.Shape(N, L, E, H, B, T, P, 0, pc, flags, law, 1, soma.ARCH_LSTM, mask))
+        ctx.set_phase_timing(True)
+        th, db = torch.from_numpy(theta.copy()).cuda(), torch.from_numpy(data).cuda()
+        losses = torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        print(f"H={H} B={B} T={T} flags={flags}: step", flush=True)
+        ctx.spsa_step(th, seeds, 2, 1e-3, 1e-2, db, losses)
+        launches.append((ctx.phase_times()["proj_launches"], ctx.narrow_projections()))
+        torch.cuda.synchronize()
+        outs.append([x.cpu().numpy() for x in (th, losses)])
+        ctx.close()
+    n = (L - 1) * ((P + (pc or P) - 1) // (pc or P))
+    assert launches == [(n, n), (n, 0)]
+    for a, b in zip(*outs):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("H", [32, 48, 80, 96, 112, 144])
+def test_resident_projection_of_an_evaluation(H):
+    """Many experts: an evaluation's slots fill the chip too, perturbed by a radius of zero
+    (no flags) and unperturbed (the kernels of the launch per step)."""
+    torch = require_gpu()
+    N, L, E, B, T, P = 512, 2, 16, 5, 16, 1
+    theta = torch.from_numpy(synth.init_theta(N, L, E, H, init_seed=7)).cuda()
+    data = torch.from_numpy(np.repeat(synth.expert_batches([95], B, T), N, axis=0)).cuda()
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    outs = []
+    for flags in (0, soma.FLAG_PER_STEP_RECURRENCE, soma.FLAG_PER_STEP_RECURRENCE | soma.FLAG_TILED_WEIGHTS):
+        ctx = soma.Context(soma.Shape(N, L, E, H, B, T, P, flags=flags))
+        loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+        losses = torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        print(f"H={H} flags={flags}: step, evaluation", flush=True)
+        ctx.spsa_step(theta.clone(), seeds, 2, 1e-3, 1e-2, data, losses)
+        before = ctx.narrow_projections()
+        ctx.eval_loss(theta, data, loss)
+        assert ctx.narrow_projections() - before == (0 if flags & soma.FLAG_TILED_WEIGHTS else 1)
+        torch.cuda.synchronize()
+        outs.append(loss.cpu().numpy())
+        ctx.close()
+    assert np.isfinite(outs[0]).all() and np.all(outs[0] == outs[0][0])
+    assert np.array_equal(outs[1], outs[2])
+    assert_losses_close(outs[0], outs[1])
