@@ -229,19 +229,19 @@ __device__ __forceinline__ float tanh_f(float x) {
 // Sum of logarithms of fp64 values in [2^-85, 2^101] (the rows' exponential
 // sums): eight factors are multiplied before a logarithm is taken, which costs
 // a hundred times a product and stood in every time step's serial chain.  The
-// product of eight stays within 2^+-808 and carries 8 x 2^-53.
+// product of eight stays within 2^+-808 and carries 8 x 2^-53.  The caller
+// numbers the factors (its tile or time step, a scalar: a count of its own and a
+// sum of logarithms apart from the caller's were registers that k_head_fused
+// spilled at H = 128, inside its loop).
 struct LogSum {
-  double sum = 0.0, prod = 1.0;
-  int n = 0;
-  __device__ __forceinline__ void add(double v) {
+  double prod = 1.0;
+  __device__ __forceinline__ void add(double v, int i, double& sum) {
     prod *= v;
-    if (++n == 8) {
+    if ((i & 7) == 7) {
       sum += log(prod);
       prod = 1.0;
-      n = 0;
     }
   }
-  __device__ __forceinline__ double total() const { return sum + log(prod); }
 };
 
 // Shape and workspace pointers shared by the forward kernels.
@@ -1663,7 +1663,8 @@ void k_rec_local(FwdArgs a, int jobs) {
   // subtracted in fp64, summed per row in fp64.
   double cacc = 0.0;
   LogSum clog;
-  auto head_combine = [&](int par) {
+  auto head_combine = [&](int tau) {                    // step tau, its partials in parity (tau + 1) & 1
+    const int par = (tau + 1) & 1;
     const int n = threadIdx.x;
     if (kHead && n < B) {
       float M = 0.0f;
@@ -1682,7 +1683,7 @@ void k_rec_local(FwdArgs a, int jobs) {
 #pragma unroll
         for (int w = 0; w < 8; ++w) S += static_cast<double>(red[(par * 8 + w) * ROWS + n].y);
       }
-      clog.add(S);
+      clog.add(S, tau, cacc);
       cacc += static_cast<double>(M) - static_cast<double>(tgl[par * ROWS + n]);
     }
   };
@@ -1811,7 +1812,7 @@ void k_rec_local(FwdArgs a, int jobs) {
     for (int t = 0; t + 1 < T; ++t) {
       if (t > 0) h_products(acc, (t & 1) ^ 1, true);    // h_{t-1}: buffer (t - 1) & 1
       if constexpr (kHead) {
-        if (t > 1) head_combine((t - 1) & 1);
+        if (t > 1) head_combine(t - 2);
         if (t > 0) head_partials(t - 1, t & 1);
       }
       cells(acc, t, t & 1);
@@ -1825,12 +1826,12 @@ void k_rec_local(FwdArgs a, int jobs) {
       // The last step's logits (h_{T-2}, buffer (T - 2) & 1), then the
       // block's cross-entropy sum: part[slot][0], the other tiles 0.
       const int tl = T - 2;
-      if (tl > 0) head_combine(tl & 1);
+      if (tl > 0) head_combine(tl - 1);
       h_products(acc, tl & 1, false);
       head_partials(tl, (tl + 1) & 1);
       __syncthreads();
-      head_combine((tl + 1) & 1);
-      if (threadIdx.x < ROWS) dsum[threadIdx.x] = cacc + clog.total();
+      head_combine(tl);
+      if (threadIdx.x < ROWS) dsum[threadIdx.x] = cacc + log(clog.prod);
       __syncthreads();
       if (threadIdx.x == 0) {
         double tot = 0.0;
@@ -2314,8 +2315,8 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
   // by B (rows past R read past the batch: 0 from the buffer, never used).
   int ytt = lr / B, yb = lr - (lr / B) * B;
   const int q64 = 64 / B, r64 = 64 % B;
-  double cacc = 0.0;                          // this combining lane's ce sum (rows 16 wave + lane of every tile),
-  LogSum clog;                                // the logarithms apart
+  double cacc = 0.0;                          // this combining lane's ce sum (rows 16 wave + lane of every tile)
+  LogSum clog;                                // and its factors not yet logged
   f32x4 acc[4];
   // Rows of tile cc from the 16 waves' partials (waves 0..3, one per SIMD,
   // 16 rows each), summed, logged and the target subtracted in fp64: a loss
@@ -2339,7 +2340,7 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) S += static_cast<double>(red[cb][w][n].y);
       }
-      clog.add(S);
+      clog.add(S, cc, cacc);
       cacc += static_cast<double>(M) - static_cast<double>(tgl[cb][n]);
     }
   };
@@ -2415,7 +2416,7 @@ __global__ __launch_bounds__(kHeadFusedThreads) void k_head_fused(FwdArgs a) {
   }
   combine(ntiles - 1);
   // The slot's total into its first tile partial, zeros in the others.
-  if (wave < 4 && lane < 16) dsum[wave * 16 + lane] = cacc + clog.total();
+  if (wave < 4 && lane < 16) dsum[wave * 16 + lane] = cacc + log(clog.prod);
   __syncthreads();
   double* part = a.part + slot * a.row_tiles;
   if (threadIdx.x == 0) {
