@@ -280,8 +280,8 @@ size_t xchg_ring_bytes(const soma_config& c) {
   return size_t(xchg_max_groups(H)) * 2 * soma::kXchgRows * H * 4;
 }
 
-// Flags, then the per-compute-unit and per-XCD placement counters.
-int xchg_counter_words() { return soma::kXchgMaxGroups * soma::kXchgFlagWords + soma::kXchgCuSlots + 8; }
+// Flags, then the per-compute-unit and per-rank placement counters.
+int xchg_counter_words() { return soma::kXchgMaxGroups * soma::kXchgFlagWords + soma::kXchgCuSlots + 8 * soma::kXchgMaxPerCu; }
 
 // Rows of one slot's gate inputs in the workspace (the larger of the two orders).
 int64_t gin_rows(const soma_config& c) {
@@ -381,8 +381,9 @@ struct soma_ctx {
   // device facts for the persistent recurrence
   int cus;                          // compute units of the device
   int coop_blocks;                  // co-resident k_rec_persist blocks (0: path unavailable)
-  int xchg_cus_per_xcd;             // k_rec_xchg blocks per XCD, one per compute unit (0: unavailable)
-  int xchg_pad_lds;                 // unused dynamic LDS per block that caps its occupancy at one
+  int xchg_per_cu;                  // co-resident k_rec_xchg blocks per compute unit (0: unavailable)
+  int xchg_cus_per_xcd;
+  int xchg_pad_lds;                 // unused dynamic LDS per block that caps its occupancy at xchg_per_cu
   float* head;                      // SOMA_ARCH_BODY, SOMA_ARCH_WIDE: the tied matrix E of expert 0 (caller owned)
   int64_t head_stride;              // floats from one expert's E to the next
   std::vector<hipEvent_t> events;   // pool, grows on demand
@@ -993,9 +994,9 @@ const void* xchg_kernel(const soma_config& c, bool layer1) {
 // group, the compute units of an XCD past its whole groups idle.
 int xchg_groups(const soma_ctx* ctx) {
   const soma_config& c = ctx->cfg;
-  if (!xchg_shape(c) || ctx->xchg_cus_per_xcd <= 0) return 0;
+  if (!xchg_shape(c) || ctx->xchg_per_cu <= 0) return 0;
   const int ut = rec_width(c) / 32;
-  const int groups = 8 * (ctx->xchg_cus_per_xcd / ut);
+  const int groups = 8 * (ctx->xchg_per_cu * ctx->xchg_cus_per_xcd / ut);
   return groups >= 8 && groups <= xchg_max_groups(rec_width(c)) ? groups : 0;
 }
 
@@ -1181,10 +1182,11 @@ int launch_xchg(soma_ctx* ctx, const soma::FwdArgs& a, int xgroups, int slots, b
   p.xh = reinterpret_cast<_Float16*>(ctx->ws + L.xch);
   p.flag = reinterpret_cast<unsigned*>(ctx->ws + L.xch + L.xch_bytes);
   p.cu_count = p.flag + soma::kXchgMaxGroups * soma::kXchgFlagWords;
-  p.xcd_count = p.cu_count + soma::kXchgCuSlots;
+  p.rank_count = p.cu_count + soma::kXchgCuSlots;
   p.err = a.err;
   p.groups = xgroups;
   p.cus_per_xcd = ctx->xchg_cus_per_xcd;
+  p.per_cu = ctx->xchg_per_cu;
   p.bblocks = (ctx->cfg.batch + soma::kXchgRows - 1) / soma::kXchgRows;
   p.jobs = slots * p.bblocks;
   p.spin_limit = ctx->spin_limit;
@@ -1193,7 +1195,7 @@ int launch_xchg(soma_ctx* ctx, const soma::FwdArgs& a, int xgroups, int slots, b
   const int words = xchg_counter_words();
   hipLaunchKernelGGL(soma::k_zero_u32, dim3((words + 255) / 256), dim3(256), 0, st, p.flag, words);
   if (int rc = check_launch("k_zero_u32")) return rc;
-  const int blocks = 8 * ctx->xchg_cus_per_xcd;
+  const int blocks = ctx->xchg_per_cu * 8 * ctx->xchg_cus_per_xcd;
   if (int rc = launch_persist(xchg_kernel(ctx->cfg, layer1), p, blocks, 512, st, unsigned(ctx->xchg_pad_lds)))
     return rc;
   ctx->rec_launches += 1;
@@ -1715,6 +1717,7 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
     }
     (void)hipGetLastError();  // a failed query only disables the persistent path
   }
+  ctx->xchg_per_cu = 0;
   ctx->xchg_cus_per_xcd = 0;
   ctx->xchg_pad_lds = 0;
   if (xchg_shape(*cfg)) {
@@ -1748,6 +1751,7 @@ void init_ctx(soma_ctx* ctx, const soma_config& cfg0, const Layout& L, char* ws,
       if (got == 1) pad_of[l1] = pad;
     }
     if (pad_of[0] >= 0 && pad_of[1] >= 0) {
+      ctx->xchg_per_cu = 1;
       ctx->xchg_cus_per_xcd = cus / 8;
       ctx->xchg_pad_lds = std::max(pad_of[0], pad_of[1]);
     }

@@ -1319,7 +1319,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_rec_persist(PersistArgs p) {
 // LDS DMA it shares with the batched products (soma_mm.hpp).
 constexpr int kXchgMaxGroups = 256;    // groups of one launch (flags in the workspace)
 constexpr int kXchgFlagWords = 256;    // flag words per group: [tile][block], H / 32 <= 64 blocks
-constexpr int kXchgCuSlots = 8 * 64;   // compute-unit claim words: (XCD, shader engine, CU)
+constexpr int kXchgCuSlots = 8 * 64;   // blocks-per-compute-unit counters: (XCD, shader engine, CU)
+constexpr int kXchgMaxPerCu = 4;
 constexpr int kXchgTiles = 4;          // row tiles of a job
 constexpr int kXchgRows = 16 * kXchgTiles;
 constexpr unsigned kAbortPlace = 4u;   // a block found no (group, tile) to claim
@@ -1329,10 +1330,11 @@ struct XchgArgs {
   _Float16* xh;          // [groups][2][tiles][H/32][hi, lo][64 words][8] published h, split
   unsigned* flag;        // [groups][kXchgFlagWords] steps published per (tile, block), over all jobs
   unsigned* cu_count;    // [kXchgCuSlots] blocks started per compute unit (zero at launch)
-  unsigned* xcd_count;   // [8] blocks placed per XCD (zero at launch)
+  unsigned* rank_count;  // [8][kXchgMaxPerCu] blocks claimed per (XCD, rank on the CU) (zero at launch)
   unsigned* err;         // sticky abort flag
   int groups;            // 8 * groups per XCD
   int cus_per_xcd;       // compute units per XCD
+  int per_cu;            // blocks per compute unit of the launch
   int jobs;              // slots of this pass (N * directions * signs) * bblocks
   int bblocks;           // 64-sequence blocks of the batch
   unsigned spin_limit;   // polls per wait before giving up

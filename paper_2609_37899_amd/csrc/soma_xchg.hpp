@@ -164,23 +164,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int H = a.H, B = a.B, T = a.T, in = a.in_l;
   const int UT = H / NU;                                // blocks per group
 
-  // Claim (group, unit tile): i = how many blocks on this XCD claimed before,
-  // UT consecutive i per group, those past the XCD's whole groups idle.  One
-  // block per compute unit: a second one is an error.  (A launch that placed two
-  // blocks on each faulted the device at H = 128, B = 10, cause not found; the
-  // host allows no such occupancy and nothing here places a second block.)
+  // Claim (group, unit tile): rank r = how many blocks started on this
+  // compute unit before this one, i = how many blocks of rank r on this XCD
+  // claimed before; position r * cus_per_xcd + i of the XCD's per_cu *
+  // cus_per_xcd blocks, UT consecutive positions per group, positions past
+  // the XCD's whole groups idle.
   if (threadIdx.x == 0) {
     const unsigned hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);         // HW_ID
     const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15;  // XCC_ID
     const unsigned cu = ((hw >> 13) & 3) * 16 + ((hw >> 8) & 15);          // shader engine, compute unit
     int grp = -2, tile = 0;                             // -2: unplaced (an error), -1: idle
-    if (xcc < 8 && __hip_atomic_fetch_add(&p.cu_count[xcc * 64 + cu], 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT) == 0u) {
-      const unsigned i = __hip_atomic_fetch_add(&p.xcd_count[xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (i < static_cast<unsigned>(p.cus_per_xcd)) {
-        const int pos = static_cast<int>(i);
-        grp = pos < (p.groups / 8) * UT ? (pos / UT) * 8 + static_cast<int>(xcc) : -1;
-        tile = pos % UT;
+    if (xcc < 8) {
+      const unsigned r = __hip_atomic_fetch_add(&p.cu_count[xcc * 64 + cu], 1u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+      if (r < static_cast<unsigned>(p.per_cu)) {
+        const unsigned i = __hip_atomic_fetch_add(&p.rank_count[xcc * kXchgMaxPerCu + r], 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        if (i < static_cast<unsigned>(p.cus_per_xcd)) {
+          const int pos = static_cast<int>(r) * p.cus_per_xcd + static_cast<int>(i);
+          grp = pos < (p.groups / 8) * UT ? (pos / UT) * 8 + static_cast<int>(xcc) : -1;
+          tile = pos % UT;
+        }
       }
     }
     if (grp == -2) __hip_atomic_fetch_or(p.err, kAbortPlace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
