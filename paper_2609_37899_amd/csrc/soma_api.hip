@@ -381,7 +381,7 @@ struct soma_ctx {
   // device facts for the persistent recurrence
   int cus;                          // compute units of the device
   int coop_blocks;                  // co-resident k_rec_persist blocks (0: path unavailable)
-  int xchg_per_cu;                  // co-resident k_rec_xchg blocks per compute unit (0: unavailable)
+  int xchg_per_cu;                  // k_rec_xchg blocks per compute unit: 1, or 0 (unavailable)
   int xchg_cus_per_xcd;
   int xchg_pad_lds;                 // unused dynamic LDS per block that caps its occupancy at xchg_per_cu
   float* head;                      // SOMA_ARCH_BODY, SOMA_ARCH_WIDE: the tied matrix E of expert 0 (caller owned)
@@ -1177,6 +1177,9 @@ int launch_persist(const void* kernel, const Args& p, int blocks, int threads, h
 int launch_xchg(soma_ctx* ctx, const soma::FwdArgs& a, int xgroups, int slots, bool layer1, bool split_out,
                 hipStream_t st) {
   const Layout& L = ctx->lay;
+  // Two exchange blocks on a compute unit faulted the device (H = 128, B = 10;
+  // cause not found): one, or none.
+  if (ctx->xchg_per_cu != 1) return fail(SOMA_EDEVICE, "k_rec_xchg runs one block per compute unit");
   soma::XchgArgs p{};
   p.a = a;
   p.xh = reinterpret_cast<_Float16*>(ctx->ws + L.xch);

@@ -168,7 +168,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // compute unit before this one, i = how many blocks of rank r on this XCD
   // claimed before; position r * cus_per_xcd + i of the XCD's per_cu *
   // cus_per_xcd blocks, UT consecutive positions per group, positions past
-  // the XCD's whole groups idle.
+  // the XCD's whole groups idle.  The host launches with per_cu = 1 only: a
+  // launch that placed two blocks on each compute unit faulted the device (H =
+  // 128, B = 10, cause not found).  (per_cu as a constant costs two to three per
+  // cent at H = 640 and 704: the main loop spills more.)
   if (threadIdx.x == 0) {
     const unsigned hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);         // HW_ID
     const unsigned xcc = __builtin_amdgcn_s_getreg((31 << 11) | 20) & 15;  // XCC_ID
