@@ -1321,6 +1321,23 @@ int run_body(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   return mark(ctx, kPhaseRec, st);
 }
 
+// LayerNorm of every row of a pass, 16 rows a block.  Four rows a wave keep enough
+// loads in flight for HBM at wide rows; at narrow ones they are a chain, and LDS
+// sized for the widest rows leaves four blocks a compute unit: one row a wave at
+// d_p = 64 (32 slots of 8 rows 7.0 -> 3.5 us a launch with the residual, of 4,224
+// 59 -> 49), two at 128 (4,224 rows 68 -> 46).
+template <int kMode>
+int launch_wide_ln(const soma::WideArgs& a, int slots, hipStream_t st) {
+  const dim3 grid(unsigned((int64_t(a.T - 1) * a.B + 15) / 16), unsigned(slots));
+  if (a.dp == 64)
+    hipLaunchKernelGGL((soma::k_wide_ln<kMode, 1, 1>), grid, dim3(1024), 0, st, a);
+  else if (a.dp == 128)
+    hipLaunchKernelGGL((soma::k_wide_ln<kMode, 2, 2>), grid, dim3(512), 0, st, a);
+  else
+    hipLaunchKernelGGL((soma::k_wide_ln<kMode, 4, 8>), grid, dim3(256), 0, st, a);
+  return check_launch("k_wide_ln");
+}
+
 // The wide controls' body: one pass of the kernels listed in soma_wide.hpp
 // over the pass's slots (expert, direction, sign), or over the experts
 // unperturbed (!kPert).
@@ -1347,6 +1364,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   a.E = ctx->head;
   a.e_stride = ctx->head_stride;
   a.wform = reinterpret_cast<float*>(ctx->ws + L.wform);
+  a.esplit = reinterpret_cast<float*>(ctx->ws + L.esplit);
   a.U = reinterpret_cast<float*>(ctx->ws + L.U);
   a.x = reinterpret_cast<float*>(ctx->ws + L.xres);
   a.n = reinterpret_cast<float*>(ctx->ws + L.hseq);
@@ -1383,13 +1401,9 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   }
   hipLaunchKernelGGL((soma::k_wide_form<kPert>),
                      dim3(unsigned((dt + soma::kFormThreads - 1) / soma::kFormThreads),
-                          unsigned(soma::wide_form_rows(dt, D)), unsigned(slots)),
+                          unsigned(soma::wide_form_rows(dt, D) + soma::kFormSplitRows), unsigned(slots)),
                      dim3(soma::kFormThreads), 0, st, a);
   if (int rc = check_launch("k_wide_form")) return rc;
-  float* esplit = reinterpret_cast<float*>(ctx->ws + L.esplit);
-  hipLaunchKernelGGL(soma::k_wide_split, dim3(SOMA_VOCAB * 4 / 256, unsigned(N)), dim3(256), 0, st, ctx->head,
-                     ctx->head_stride, esplit, err);
-  if (int rc = check_launch("k_wide_split")) return rc;
   if (int rc = mark(ctx, kPhaseFold, st)) return rc;
 
   soma::MmArgs m{};
@@ -1400,7 +1414,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   m.w_slot = F.total;
   m.B = c.batch % 16 == 0 ? 0 : c.batch;
   // U = E P_in^T: the input projection of every byte value.
-  m.A = reinterpret_cast<const _Float16*>(esplit);
+  m.A = reinterpret_cast<const _Float16*>(a.esplit);
   m.a_slot = int64_t(SOMA_VOCAB) * soma::kWideHeadWidth;
   m.a_expert = 1;
   m.W = reinterpret_cast<const _Float16*>(a.wform + F.pin);
@@ -1410,9 +1424,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   m.N = dp;
   m.K = soma::kWideHeadWidth;
   if (int rc = launch_mm<soma::kEpiStore>(m, slots, ctx->cus, st)) return rc;
-  const dim3 ln_grid(unsigned((R + 15) / 16), unsigned(slots));
-  hipLaunchKernelGGL((soma::k_wide_ln<0>), ln_grid, dim3(256), 0, st, a);
-  if (int rc = check_launch("k_wide_ln")) return rc;
+  if (int rc = launch_wide_ln<0>(a, slots, st)) return rc;
   if (int rc = mark(ctx, kPhaseFold, st)) return rc;
 
   m.a_expert = 0;
@@ -1482,8 +1494,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     }
     if (int rc = mark(ctx, kPhaseRec, st)) return rc;
     // x += h; n = LN(x); m = GELU(n U'^T); x += m V^T
-    hipLaunchKernelGGL((soma::k_wide_ln<1>), ln_grid, dim3(256), 0, st, a);
-    if (int rc = check_launch("k_wide_ln")) return rc;
+    if (int rc = launch_wide_ln<1>(a, slots, st)) return rc;
     m.A = reinterpret_cast<const _Float16*>(a.n);
     m.a_slot = R16 * dp;
     m.W = reinterpret_cast<const _Float16*>(blk + 2 * mp);
@@ -1501,14 +1512,12 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
     m.K = 4 * dp;
     if (int rc = launch_mm<soma::kEpiAdd>(m, slots, ctx->cus, st)) return rc;
     if (l + 1 < D) {
-      hipLaunchKernelGGL((soma::k_wide_ln<2>), ln_grid, dim3(256), 0, st, a);
-      if (int rc = check_launch("k_wide_ln")) return rc;
+      if (int rc = launch_wide_ln<2>(a, slots, st)) return rc;
     }
     if (int rc = mark(ctx, kPhaseProj, st)) return rc;
     ctx->proj_launches += 2;
   }
-  hipLaunchKernelGGL((soma::k_wide_ln<2>), ln_grid, dim3(256), 0, st, a);
-  if (int rc = check_launch("k_wide_ln")) return rc;
+  if (int rc = launch_wide_ln<2>(a, slots, st)) return rc;
   // u = n P_out'^T into the (free) gate-input buffer, then the decoder.
   m.A = reinterpret_cast<const _Float16*>(a.n);
   m.a_slot = R16 * dp;

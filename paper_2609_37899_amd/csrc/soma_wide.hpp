@@ -16,8 +16,8 @@
 // A pass of this body runs, for every slot (expert, direction, sign):
 //   k_wide_form   perturbed weights, gains folded into the matrices that
 //                 read a normalised vector, zero-padded to d_p = 64 ceil(d_t
-//                 / 64), in fragment order (once per pass)
-//   k_wide_split  each expert's E in fragment order
+//                 / 64), and each expert's E, in fragment order (once per
+//                 pass)
 //   k_mm          U = E P_in^T (the input projection per byte value)
 //   k_wide_ln     x = U[byte], n = LN(x)   (the gain sits in the weights)
 //   per block:    k_mm gin = n A'           (gate inputs, units interleaved)
@@ -69,6 +69,7 @@ struct WideArgs {
   const float* E;         // tied matrices, expert e at E + e * e_stride, [256][32]
   int64_t e_stride;
   float* wform;           // pre-formed weights, [slots][WideForm::total]
+  float* esplit;          // E in fragment order, [N][256][32] split pairs
   float* U;               // [slots][256][d_p]
   float* x;               // [slots][R][d_p] residual stream
   float* n;               // [slots][ceil(R / 16) 16][d_p] normalised x in fragment order (also h of the recurrence, fp32)
@@ -135,7 +136,7 @@ __device__ __forceinline__ float wide_coord(const float* th, int64_t k, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Pre-formed weights of every slot, in fragment order.  A thread forms 16-byte
+// Pre-formed weights of every slot, and E, in fragment order.  A thread forms 16-byte
 // words, so that stores are words and not halves:
 //  * matrices whose canonical rows run along K's other side (A, R, U [c][j] and
 //    P_out [c][q]; K index c): eight rows c of one column quad, i.e. eight
@@ -152,10 +153,27 @@ __device__ __forceinline__ float wide_coord(const float* th, int64_t k, int64_t 
 constexpr int kFormThreads = 128;
 
 // Row groups along c, and the rows of blockIdx.y: 3 D matrices (A, R, U of
-// each block) and P_out by groups of eight c, then V and P_in by rows c.
+// each block) and P_out by groups of eight c, then V and P_in by rows c, then
+// the words of the experts' E.
 __host__ __device__ inline int wide_form_groups(int dt) { return (dt + 7) / 8; }
 __host__ __device__ inline int wide_form_rows(int dt, int D) {
   return (3 * D + 1) * wide_form_groups(dt) + (D + 1) * dt;
+}
+constexpr int kFormSplitRows = kVocab * 4 / kFormThreads;
+
+// Each expert's tied matrix E [256][32] in fragment order (256 x 32 split
+// pairs at esplit + expert * 8192): one word per thread.
+__device__ __forceinline__ bool wide_split_word(const float* E, _Float16* esplit, int i) {
+  constexpr int K = kWideHeadWidth;
+  const int row = i >> 2, g = i & 3;                    // 4 words of hi a row
+  const float* src = E + row * K + 8 * g;
+  const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
+  uint4 hi, lo;
+  split8v(x, y, hi, lo);
+  _Float16* w = esplit + int64_t(row >> 4) * 2 * 512 + (16 * g + (row & 15)) * 8;
+  *reinterpret_cast<uint4*>(w) = hi;
+  *reinterpret_cast<uint4*>(w + 512) = lo;
+  return split_range_ok(x) && split_range_ok(y);
 }
 
 template <bool kPert>
@@ -229,6 +247,11 @@ __global__ __launch_bounds__(kFormThreads) void k_wide_form(WideArgs a) {
             make_float4(v[4][q], v[5][q], v[6][q], v[7][q]));
       }
     }
+  } else if (y >= wide_form_rows(dt, D)) {              // E, once per expert
+    if (blockIdx.x == 0 && jl == 0 && sg == 0)
+      ok = wide_split_word(a.E + int64_t(e) * a.e_stride,
+                           reinterpret_cast<_Float16*>(a.esplit + int64_t(e) * kVocab * kWideHeadWidth),
+                           (y - wide_form_rows(dt, D)) * kFormThreads + static_cast<int>(threadIdx.x));
   } else {
     y -= (3 * D + 1) * groups;
     const int l = y / dt, c = y % dt;                   // V of block l, or P_in (l == D)
@@ -245,23 +268,6 @@ __global__ __launch_bounds__(kFormThreads) void k_wide_form(WideArgs a) {
   report_split_range(a.err, ok);
 }
 
-// Each expert's tied matrix E [256][32] in fragment order (256 x 32 split
-// pairs at esplit + expert * 8192): one word per thread, one expert per
-// blockIdx.y.
-__global__ __launch_bounds__(256) void k_wide_split(const float* E, int64_t e_stride, float* esplit, unsigned* err) {
-  constexpr int K = kWideHeadWidth;
-  const int i = blockIdx.x * 256 + threadIdx.x, row = i >> 2, g = i & 3;   // 4 words of hi a row
-  const float* src = E + int64_t(blockIdx.y) * e_stride + row * K + 8 * g;
-  const float4 x = *reinterpret_cast<const float4*>(src), y = *reinterpret_cast<const float4*>(src + 4);
-  uint4 hi, lo;
-  split8v(x, y, hi, lo);
-  _Float16* w = reinterpret_cast<_Float16*>(esplit + int64_t(blockIdx.y) * kVocab * K) + int64_t(row >> 4) * 2 * 512 +
-                (16 * g + (row & 15)) * 8;
-  *reinterpret_cast<uint4*>(w) = hi;
-  *reinterpret_cast<uint4*>(w + 512) = lo;
-  report_split_range(err, split_range_ok(x) && split_range_ok(y));
-}
-
 // out[i] = 0 for i < n (a fill kernel, so that callers may capture it).
 __global__ void k_fill_f32(float* out, int64_t n) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
@@ -269,8 +275,8 @@ __global__ void k_fill_f32(float* out, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// Gain-free LayerNorm of every row of x, a row tile of 16 per block, four rows
-// a wave one after another:
+// Gain-free LayerNorm of every row of x, a row tile of 16 per block, RPW rows a
+// wave one after another, d_p <= 64 kMaxC:
 //   kMode 0: x = U[byte]          (the embedding's projection per byte value)
 //   kMode 1: x += h               (the LSTM sublayer's residual; h in n)
 //   kMode 2: x as it is
@@ -279,9 +285,8 @@ __global__ void k_fill_f32(float* out, int64_t n) {
 // and written in fragment order over the 16 fp32 rows of h it replaces (read by
 // this block alone, before its barrier).  Rows are r = t B + b.
 // ---------------------------------------------------------------------------
-template <int kMode>
-__global__ __launch_bounds__(256) void k_wide_ln(WideArgs a) {
-  constexpr int kMaxC = 8;   // d_p <= 512
+template <int kMode, int RPW, int kMaxC>
+__global__ __launch_bounds__(1024 / RPW) void k_wide_ln(WideArgs a) {
   constexpr int LD = 64 * kMaxC + 4;                    // LDS row in split pairs
   __shared__ uint32_t tile[16][LD];                     // (hi, lo) of every value
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -294,10 +299,10 @@ __global__ __launch_bounds__(256) void k_wide_ln(WideArgs a) {
   const int dp = a.dp, dt = a.dt, nc = dp / 64;
   const int64_t n_rows = (R + 15) / 16 * 16;
   // The wave's rows are all requested before the first is used.
-  float v[4][kMaxC];
+  float v[RPW][kMaxC];
 #pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    const int64_t r = r0 + wave * 4 + rr;
+  for (int rr = 0; rr < RPW; ++rr) {
+    const int64_t r = r0 + wave * RPW + rr;
 #pragma unroll
     for (int i = 0; i < kMaxC; ++i) v[rr][i] = 0.0f;
     if (r >= R) continue;                               // wave-uniform
@@ -312,22 +317,22 @@ __global__ __launch_bounds__(256) void k_wide_ln(WideArgs a) {
       if (i < nc) v[rr][i] = src[64 * i + lane];
   }
   if (kMode == 1) {
-    float h[4][kMaxC];
+    float h[RPW][kMaxC];
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      const int64_t r = r0 + wave * 4 + rr;
+    for (int rr = 0; rr < RPW; ++rr) {
+      const int64_t r = r0 + wave * RPW + rr;
       const float* nr = a.n + (slot * n_rows + r) * dp;
 #pragma unroll
       for (int i = 0; i < kMaxC; ++i) h[rr][i] = i < nc && r < R ? nr[64 * i + lane] : 0.0f;
     }
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr)
+    for (int rr = 0; rr < RPW; ++rr)
 #pragma unroll
       for (int i = 0; i < kMaxC; ++i) v[rr][i] += h[rr][i];
   }
 #pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    const int row = wave * 4 + rr;
+  for (int rr = 0; rr < RPW; ++rr) {
+    const int row = wave * RPW + rr;
     const int64_t r = r0 + row;
     if (kMode != 2 && r < R) {
       float* xr = a.x + (slot * R + r) * dp;
@@ -364,7 +369,7 @@ __global__ __launch_bounds__(256) void k_wide_ln(WideArgs a) {
   // and lo blocks.
   _Float16* dst = reinterpret_cast<_Float16*>(a.n + (slot * n_rows + r0) * dp);
   const int KC = dp / 32;
-  for (int w = threadIdx.x; w < KC * 64; w += 256) {
+  for (int w = threadIdx.x; w < KC * 64; w += 1024 / RPW) {
     const int kc = w >> 6, row = w & 15, g = (w >> 4) & 3;
     const uint4 p0 = *reinterpret_cast<const uint4*>(&tile[row][32 * kc + 8 * g]);
     const uint4 p1 = *reinterpret_cast<const uint4*>(&tile[row][32 * kc + 8 * g + 4]);
