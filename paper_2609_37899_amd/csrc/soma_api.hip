@@ -254,17 +254,49 @@ int64_t tile_rows(const soma_config& c) { return int64_t(c.seq_len - 1) * ((c.ba
 // them filled it is still ahead of the staged recurrence, which computes four
 // as well (H = 128, B = 33, 128 jobs of 99 steps: 0.81 against 0.98 ms a
 // layer) -- at every width its registers hold: H a multiple of 64 up to 704 (up to 512 on the wide body's pre-formed weights;
-// the stacked LSTM at H = 64 has k_rec_local).  Batches beyond 64 are cut into
-// jobs of 64, from four time steps on: below that the launch per step is ahead
-// (eight slots of 100 sequences, two layers, H = 128: one step 75 against
-// 134 us, eight 361 against 210; H = 704: 211 against 443, 1,314 against 829).
-// It addresses a slot's gate inputs with 32-bit offsets.  Whether
-// it runs also depends on the device (compute units per XCD).
+// the stacked LSTM at H = 64 has k_rec_local), from the window length of
+// xchg_min_len on.  Batches beyond 64 are cut into jobs of 64.  It addresses a
+// slot's gate inputs with 32-bit offsets.  Whether it runs also depends on the
+// device (compute units per XCD).
+int64_t xchg_jobs(const soma_config& c) {   // of a whole step: the direction chunk must not change its route
+  return int64_t(2) * c.n_experts * dirs(c) * ((c.batch + soma::kXchgRows - 1) / soma::kXchgRows);
+}
+
+// The shortest windows it takes (stacked LSTM).  Figures: exchange over the other
+// route, whole steps, two layers unless one is said.
+//  * Up to 64 sequences the other route is the staged recurrence, which forms its
+//    weights faster.  One step: 1.02 to 1.16 (one layer); 1.03 to 1.25 from 32 jobs
+//    on at H <= 256 and above 512, 0.97 to 1.02 between, where 64 jobs are 1.08 and
+//    128 up to 1.13; with few jobs the next layer's k_mm is worth more (two 0.94 to
+//    1.03).  Two steps: 0.9 to 1.05, but at H = 704 with the Rademacher laws, whose
+//    draws are cheap, from 32 jobs on 1.05 to 1.10.
+//  * Beyond 64 it is the launch per step, which forms them every step but on every
+//    compute unit: ahead below four steps (eight slots of 100 sequences: H = 128 one
+//    step 75 against 134 us, H = 704 211 against 443), and where an XCD's whole
+//    groups leave 8 or more of its 32 compute units idle (H = 384 and above 512) up
+//    to more steps the more jobs a group takes one after another.  B = 65 to 128: H =
+//    384, four steps, 32 jobs 0.84, 64 1.04 to 1.09; five, 256 0.92 to 1.0.  H = 576
+//    to 704, four, 16 jobs 0.85 to 0.91, 32 1.06 to 1.18; five, 32 0.91 to 1.04, 64 1.01
+//    to 1.09; six, 64 0.90 to 0.98, 256 0.96 to 1.13; seven, 256 0.89 to 1.05.  With the
+//    Rademacher laws one step more: six, 64 0.93 to 1.07; seven, 64 0.87 to 1.02, 256
+//    0.97 to 1.12; eight, 256 0.91 to 1.04.
+int xchg_min_len(const soma_config& c) {
+  const int64_t jobs = xchg_jobs(c);
+  const bool gauss = c.probe == SOMA_PROBE_GAUSSIAN;
+  if (c.batch <= 64) {
+    if (!gauss && c.hidden > 640 && jobs > 16) return 4;
+    return c.n_layers == 1 || jobs > (c.hidden > 256 && c.hidden <= 512 ? 32 : 16) ? 3 : 2;
+  }
+  if (32 % (c.hidden / 32) < 8 || jobs <= 16) return 5;
+  if (c.hidden <= 512) return jobs <= 32 ? 5 : 6;
+  return (jobs <= 32 ? 6 : jobs <= 96 ? 7 : 8) + (gauss ? 0 : 1);
+}
+
 bool xchg_shape(const soma_config& c) {
   const int H = rec_width(c);
   if (c.arch == SOMA_ARCH_BODY || H % 64 != 0 || H > (c.arch == SOMA_ARCH_WIDE ? 512 : soma::kRecMaxH)) return false;
   if (c.arch == SOMA_ARCH_LSTM && H < 128) return false;
-  if (c.batch > 64 && c.seq_len < 5) return false;
+  if (c.arch == SOMA_ARCH_LSTM && c.seq_len < xchg_min_len(c)) return false;
   const int64_t gin_slot_bytes = tile_rows(c) * 4 * H * int64_t(sizeof(float));
   return c.batch > 32 && gin_slot_bytes < (int64_t(1) << 31) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
          !(c.flags & SOMA_FLAG_STAGED_RECURRENCE);
