@@ -74,3 +74,49 @@ def test_wide_exchange_matches_oracle(oracle_mod, dt, B):
     ref = oracle_mod.spsa_step(cfg, theta, seeds, 3, 1e-3, 1e-3, data)
     assert_losses_close(losses.cpu().numpy(), ref["losses"])
     assert_theta_close(th.cpu().numpy(), ref["theta"])
+
+
+@pytest.mark.parametrize("case", [(1, 2, 32, 256, 49, 12, 6, 0), (1, 2, 32, 128, 100, 15, 20, 1),
+                                  (2, 1, 16, 704, 33, 9, 3, 2), (1, 2, 32, 512, 65, 10, 5, 0)],
+                         ids=lambda c: "h%d_b%d_l%d" % (c[3], c[4], c[1]))
+def test_exchange_step_is_repeatable(case):
+    """Ragged row tiles, jobs of a batch beyond 64, several jobs a group: every repeat has the same bits."""
+    torch = require_gpu()
+    N, L, E, H, B, T, P, probe = case
+    theta = torch.from_numpy(synth.init_theta(N, L, E, H, init_seed=2, distinct=True)).cuda()
+    data = torch.from_numpy(synth.expert_batches([700 + e for e in range(N)], B, T)).cuda()
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    ctx = soma.Context(soma.Shape(N, L, E, H, B, T, P, probe=probe))
+    ctx.set_phase_timing(True)
+    first = None
+    for i in range(12):
+        th, losses = theta.clone(), torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        ctx.spsa_step(th, seeds, 7, 1e-3, 1e-3, data, losses)
+        assert ctx.phase_times()["xchg_launches"] == L
+        out = (th.cpu().numpy(), losses.cpu().numpy())
+        first = first or out
+        assert np.all(np.isfinite(out[1]))
+        assert np.array_equal(out[0], first[0]) and np.array_equal(out[1], first[1]), f"repeat {i}"
+
+
+@pytest.mark.parametrize("dt,B", [(130, 33), (361, 50)])
+def test_wide_exchange_step_is_repeatable(dt, B):
+    torch = require_gpu()
+    N, D, T, P = 2, 2, 10, 4
+    theta = torch.from_numpy(synth.init_wide(N, D, dt, 32, init_seed=4, distinct=True)).cuda()
+    E = torch.from_numpy(synth.init_tied_head(32, init_seed=6, n_experts=N)).cuda()
+    data = torch.from_numpy(synth.expert_batches([800 + e for e in range(N)], B, T)).cuda()
+    seeds = soma.seeds_tensor(synth.expert_seeds(N))
+    ctx = soma.Context(soma.Shape(N, D, 32, dt, B, T, P, probe=1, arch=soma.ARCH_WIDE))
+    ctx.set_tied_head(E, per_expert=True)
+    first = None
+    for i in range(8):
+        th, losses = theta.clone(), torch.zeros((N, P, 2), dtype=torch.float32, device="cuda")
+        loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+        ctx.spsa_step(th, seeds, 3, 1e-3, 1e-3, data, losses)
+        ctx.eval_loss(th, data, loss)                     # one sign a job
+        torch.cuda.synchronize()
+        out = [x.cpu().numpy() for x in (th, losses, loss)]
+        first = first or out
+        assert all(np.isfinite(x).all() for x in out)
+        assert all(np.array_equal(a, b) for a, b in zip(out, first)), f"repeat {i}"

@@ -43,7 +43,7 @@ CASES = {
 # only (the oracle would take minutes on them).
 LONG_CASES = {
     "h512_b64_t40": (1, 2, 32, 512, 64, 40, 4, 1e-3, 1e-3, 0, 0),   # fragment-order exchange, 39 steps
-    "h704_b64_t24": (1, 2, 32, 704, 64, 24, 2, 1e-3, 1e-3, 0, 0),   # 16-byte word exchange, 23 steps
+    "h704_b64_t24": (1, 2, 32, 704, 64, 24, 2, 1e-3, 1e-3, 0, 0),   # pipelined exchange at its widest, 23 steps
 }
 
 def run_case(name, distinct=True, data=None, probe=0, head_scale=1.0):
