@@ -258,12 +258,19 @@ int64_t tile_rows(const soma_config& c) { return int64_t(c.seq_len - 1) * ((c.ba
 // xchg_min_len on.  Batches beyond 64 are cut into jobs of 64.  It addresses a
 // slot's gate inputs with 32-bit offsets.  Whether it runs also depends on the
 // device (compute units per XCD).
-int64_t xchg_jobs(const soma_config& c) {   // of a whole step: the direction chunk must not change its route
-  return int64_t(2) * c.n_experts * dirs(c) * ((c.batch + soma::kXchgRows - 1) / soma::kXchgRows);
+bool xchg_fits(const soma_config& c) {
+  const int H = rec_width(c);
+  if (c.arch == SOMA_ARCH_BODY || H % 64 != 0 || H > (c.arch == SOMA_ARCH_WIDE ? 512 : soma::kRecMaxH)) return false;
+  if (c.arch == SOMA_ARCH_LSTM && H < 128) return false;
+  const int64_t gin_slot_bytes = tile_rows(c) * 4 * H * int64_t(sizeof(float));
+  return c.batch > 32 && gin_slot_bytes < (int64_t(1) << 31) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
+         !(c.flags & SOMA_FLAG_STAGED_RECURRENCE);
 }
 
-// The shortest windows it takes (stacked LSTM).  Figures: exchange over the other
-// route, whole steps, two layers unless one is said.
+// The shortest windows it takes (stacked LSTM) in a call of so many directions an
+// expert (a step's, all chunks together: the chunk must not change its route; one
+// in an evaluation).  Figures: exchange over the other route, whole steps, two
+// layers unless one is said.
 //  * Up to 64 sequences the other route is the staged recurrence, which forms its
 //    weights faster.  One step: 1.02 to 1.16 (one layer); 1.03 to 1.25 from 32 jobs
 //    on at H <= 256 and above 512, 0.97 to 1.02 between, where 64 jobs are 1.08 and
@@ -280,8 +287,9 @@ int64_t xchg_jobs(const soma_config& c) {   // of a whole step: the direction ch
 //    to 1.09; six, 64 0.90 to 0.98, 256 0.96 to 1.13; seven, 256 0.89 to 1.05.  With the
 //    Rademacher laws one step more: six, 64 0.93 to 1.07; seven, 64 0.87 to 1.02, 256
 //    0.97 to 1.12; eight, 256 0.91 to 1.04.
-int xchg_min_len(const soma_config& c) {
-  const int64_t jobs = xchg_jobs(c);
+int xchg_min_len(const soma_config& c, int directions) {
+  if (c.arch != SOMA_ARCH_LSTM) return 2;
+  const int64_t jobs = int64_t(2) * c.n_experts * directions * ((c.batch + soma::kXchgRows - 1) / soma::kXchgRows);
   const bool gauss = c.probe == SOMA_PROBE_GAUSSIAN;
   if (c.batch <= 64) {
     if (!gauss && c.hidden > 640 && jobs > 16) return 4;
@@ -292,15 +300,9 @@ int xchg_min_len(const soma_config& c) {
   return (jobs <= 32 ? 6 : jobs <= 96 ? 7 : 8) + (gauss ? 0 : 1);
 }
 
-bool xchg_shape(const soma_config& c) {
-  const int H = rec_width(c);
-  if (c.arch == SOMA_ARCH_BODY || H % 64 != 0 || H > (c.arch == SOMA_ARCH_WIDE ? 512 : soma::kRecMaxH)) return false;
-  if (c.arch == SOMA_ARCH_LSTM && H < 128) return false;
-  if (c.arch == SOMA_ARCH_LSTM && c.seq_len < xchg_min_len(c)) return false;
-  const int64_t gin_slot_bytes = tile_rows(c) * 4 * H * int64_t(sizeof(float));
-  return c.batch > 32 && gin_slot_bytes < (int64_t(1) << 31) && !(c.flags & SOMA_FLAG_PER_STEP_RECURRENCE) &&
-         !(c.flags & SOMA_FLAG_STAGED_RECURRENCE);
-}
+// Whether any call on the shape takes it (an evaluation does where a step does:
+// the line rises with the jobs).
+bool xchg_shape(const soma_config& c) { return xchg_fits(c) && c.seq_len >= xchg_min_len(c, 1); }
 
 // Groups the exchange recurrence can have at width H: 8 XCDs of at most 64
 // compute units, one block each, H / 32 blocks a group.
@@ -1021,12 +1023,12 @@ const void* xchg_kernel(const soma_config& c, bool layer1) {
   return soma::xchg_kernel_for(c.hidden, c.probe != SOMA_PROBE_GAUSSIAN, layer1);
 }
 
-// Groups of the exchange recurrence (a multiple of 8, each on one XCD), or
-// 0 where it does not run: one block per compute unit, H / 32 blocks a
+// Groups of the exchange recurrence (a multiple of 8, each on one XCD) in a call
+// of so many directions an expert, or 0 where it does not run: one block per compute unit, H / 32 blocks a
 // group, the compute units of an XCD past its whole groups idle.
-int xchg_groups(const soma_ctx* ctx) {
+int xchg_groups(const soma_ctx* ctx, int directions) {
   const soma_config& c = ctx->cfg;
-  if (!xchg_shape(c) || ctx->xchg_per_cu <= 0) return 0;
+  if (!xchg_fits(c) || c.seq_len < xchg_min_len(c, directions) || ctx->xchg_per_cu <= 0) return 0;
   const int ut = rec_width(c) / 32;
   const int groups = 8 * (ctx->xchg_per_cu * ctx->xchg_cus_per_xcd / ut);
   return groups >= 8 && groups <= xchg_max_groups(rec_width(c)) ? groups : 0;
@@ -1385,7 +1387,7 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   const soma::WideForm F = soma::wide_form_layout(dp, D);
   const int64_t mp = 4 * int64_t(dp) * dp;
   unsigned* err = reinterpret_cast<unsigned*>(ctx->ws + L.sync) + kMaxGroups;
-  const int xgroups = xchg_groups(ctx);
+  const int xgroups = xchg_groups(ctx, 1);
   const int groups = persistent_groups_h(ctx, slots, dp);
   if (groups <= 0) return fail(SOMA_EDEVICE, "the wide body needs the persistent recurrence (cooperative launch)");
 
@@ -1565,11 +1567,12 @@ int run_wide(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t 
   return mark(ctx, kPhaseHead, st);
 }
 
-// Forward passes of `pcs` directions starting at j0 (kPert) or of the
-// unperturbed experts (!kPert, pcs = 1), ending with per-tile loss sums.
+// Forward passes of `pcs` directions starting at j0, of a call's `directions`
+// (kPert), or of the unperturbed experts (!kPert, pcs = 1), ending with per-tile
+// loss sums.
 template <bool kPert>
 int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64_t step, const float* eps_v,
-                int eps_stride, const uint8_t* bytes, int j0, int pcs, hipStream_t st) {
+                int eps_stride, const uint8_t* bytes, int j0, int pcs, int directions, hipStream_t st) {
   const soma_config& c = ctx->cfg;
   if (c.arch == SOMA_ARCH_BODY) return run_body<kPert>(ctx, theta, seeds, step, eps_v, eps_stride, bytes, j0, pcs, st);
   if (c.arch == SOMA_ARCH_WIDE) return run_wide<kPert>(ctx, theta, seeds, step, eps_v, eps_stride, bytes, j0, pcs, st);
@@ -1609,7 +1612,7 @@ int run_forward(soma_ctx* ctx, const float* theta, const uint64_t* seeds, uint64
   a.layer = 0;
   a.in_l = c.embed;
   a.off_l = L.off_layer[0];
-  const int xgroups = kPert ? xchg_groups(ctx) : 0;
+  const int xgroups = kPert ? xchg_groups(ctx, directions) : 0;
   a.tiled = xgroups > 0 ? 1 : 0;   // every layer's recurrence is the exchange
   const bool emb_local = kPert && local_embedding(c);
   // One layer at H = 64 with the embedding in the block: the head and the
@@ -1980,7 +1983,7 @@ int forwards_and_coefficients(soma_ctx* ctx, const float* theta, const uint64_t*
   *err_out = err;
   if (L.pc >= D && c.loss_mode != SOMA_LOSS_SUMMED) {
     // One pass, each expert's coefficients from its own losses.
-    if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, 0, D, st)) return rc;
+    if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, 0, D, D, st)) return rc;
     hipLaunchKernelGGL(soma::k_loss_coef, dim3((nc + 3) / 4), dim3(256), 0, st, part, L.row_tiles, c.n_experts, D, L.pc,
                        inv_rows, r.eps_v, r.eps_stride, losses, lossd, coef, err);
     if (int rc = check_launch("k_loss_coef")) return rc;
@@ -1988,7 +1991,8 @@ int forwards_and_coefficients(soma_ctx* ctx, const float* theta, const uint64_t*
   }
   for (int j0 = 0; j0 < D; j0 += L.pc) {
     const int pcs = std::min(L.pc, D - j0);
-    if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, j0, pcs, st)) return rc;
+    if (int rc = run_forward<true>(ctx, theta, seeds, step, r.eps_v, r.eps_stride, bytes, j0, pcs, D, st))
+      return rc;
     const int n = c.n_experts * pcs * 2;
     hipLaunchKernelGGL(soma::k_loss_reduce, dim3((n + 3) / 4), dim3(256), 0, st, part, L.row_tiles, c.n_experts, pcs,
                        L.pc, 2, D, j0, inv_rows, losses, lossd, err);
@@ -2213,7 +2217,7 @@ int soma_eval_loss(soma_ctx* ctx, const float* theta, const uint8_t* bytes, floa
     Rates r{};
     const int rcr = scalar_rates(ctx, 0.0f, 0.0f, st, &r);
     const uint64_t* any_seeds = reinterpret_cast<const uint64_t*>(ctx->ws + L.lossd);
-    const int rc0 = rcr ? rcr : run_forward<true>(ctx, theta, any_seeds, 0, r.eps_v, 1, bytes, 0, 1, st);
+    const int rc0 = rcr ? rcr : run_forward<true>(ctx, theta, any_seeds, 0, r.eps_v, 1, bytes, 0, 1, 1, st);
     ctx->timing = timing;
     if (rc0) return rc0;
     hipLaunchKernelGGL(soma::k_eval_reduce, dim3((N + 3) / 4), dim3(256), 0, st,
@@ -2223,7 +2227,7 @@ int soma_eval_loss(soma_ctx* ctx, const float* theta, const uint8_t* bytes, floa
   }
   hipLaunchKernelGGL(soma::k_zero_u32, dim3(1), dim3(64), 0, st, err, 1);
   int rc0 = check_launch("k_zero_u32");
-  if (!rc0) rc0 = run_forward<false>(ctx, theta, nullptr, 0, nullptr, 0, bytes, 0, 1, st);
+  if (!rc0) rc0 = run_forward<false>(ctx, theta, nullptr, 0, nullptr, 0, bytes, 0, 1, 1, st);
   ctx->timing = timing;
   if (rc0) return rc0;
   hipLaunchKernelGGL(soma::k_loss_reduce, dim3((c.n_experts + 3) / 4), dim3(256), 0, st,

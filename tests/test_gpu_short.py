@@ -1,8 +1,8 @@
 """The shortest windows of the exchange recurrence, on both sides of the lines that its
 launch rule draws by jobs and idle compute units: which recurrence runs (one launch a
 layer of the exchange or the staged recurrence, or one a time step), the oracle's
-losses and weights from either, and the same bits whatever the direction chunk (the
-rule must not go by the chunk's jobs)."""
+losses and weights from either, the same bits whatever the direction chunk (the rule
+must not go by the chunk's jobs), and an evaluation by its own few jobs."""
 import numpy as np
 import pytest
 
@@ -42,10 +42,17 @@ def test_short_windows(oracle_mod, case, exchange):
         chunks = (P + (pc or P) - 1) // (pc or P)
         assert pt["xchg_launches"] == (L * chunks if exchange else 0)
         assert pt["rec_launches"] == L * chunks * (1 if exchange or B <= 64 else T - 1)
-        outs.append((th.cpu().numpy(), losses.cpu().numpy()))
+        before = torch.from_numpy(theta.copy()).cuda()
+        loss = torch.zeros(N, dtype=torch.float32, device="cuda")
+        ctx.eval_loss(before, torch.from_numpy(data).cuda(), loss)
+        least = (3 if L == 1 else 2) if B <= 64 else 5      # two or four jobs
+        assert ctx.phase_times()["xchg_launches"] - pt["xchg_launches"] == (L if T >= least else 0)
+        outs.append((th.cpu().numpy(), losses.cpu().numpy(), loss.cpu().numpy()))
         ctx.close()
-    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
     cfg = oracle_mod.make_cfg(N, L, E, H, B, T, P, probe=probe)
     ref = oracle_mod.spsa_step(cfg, theta, seeds, 7, 1e-3, 1e-3, data)
     assert_losses_close(outs[0][1], ref["losses"])
+    assert_losses_close(outs[0][2], oracle_mod.eval_loss(cfg, theta, data))
     assert_theta_close(outs[0][0], ref["theta"])
