@@ -117,9 +117,9 @@ enum soma_flags {
    * within the split products' rounding. */
   SOMA_FLAG_TILED_WEIGHTS = 2,
   /* Run the persistent recurrence with fp32 h staged by every block of a
-   * group, even where the pipelined split exchange applies (B > 32: four row
-   * tiles in flight, h published once in split form and copied into LDS by
-   * DMA).  Both form the same split products; the exchange sums them in
+   * group, even where the pipelined split exchange applies (B > 32, from a
+   * window length on that goes by width and jobs: four row tiles in flight, h
+   * published once in split form and copied into LDS by DMA).  Both form the same split products; the exchange sums them in
    * another order, so results agree within that rounding. */
   SOMA_FLAG_STAGED_RECURRENCE = 4,
   /* Store each layer's output sequence in fp32 and let the next layer's
